@@ -432,7 +432,11 @@ int wadg_set_schedule(wadg_ctx ctx, int32_t groups_per_tile, int32_t slices_per_
  *   WADG_KERNEL_AUTO (default): LSRK stages (FP64 and FP32) of two or more
  *     slices take the pipelined kernel where it fits, else the split
  *     kernel; right-hand-side launches the resident kernel where it fits,
- *     else the split kernel -- the fastest measured on MI355X.
+ *     else the split kernel -- the fastest measured on MI355X.  Launches of
+ *     few elements (all slices together: up to 24 per CU in FP64, 32 to 64
+ *     in FP32) take a kernel that spreads each element over several lanes,
+ *     and the sweep of a mesh of few elements (one workgroup: up to 64,
+ *     fewer at high degree or with many slices) runs as one launch.
  * All variants give bitwise-identical results.  The adjoint's operator
  * launches (apply-A) take the split kernel under AUTO and SPLIT, else the
  * streamed kernel (the resident kernel has no apply-A mode).  Returns
@@ -441,9 +445,9 @@ int wadg_set_schedule(wadg_ctx ctx, int32_t groups_per_tile, int32_t slices_per_
  * kernel is requested for an (N, nq1) whose FP64 data do not fit. */
 int wadg_set_kernel(wadg_ctx ctx, int32_t kernel);
 
-/* The kernel variant that `ctx` launches for LSRK stages (rhs == 0; FP64
- * for fp32 == 0, FP32-bulk for fp32 != 0) or for wadg_rhs (rhs != 0,
- * fp32 == 0).  kernel: host out. */
+/* The kernel variant that `ctx` uses in launches of many slices for LSRK
+ * stages (rhs == 0; FP64 for fp32 == 0, FP32-bulk for fp32 != 0) or for
+ * wadg_rhs (rhs != 0, fp32 == 0).  kernel: host out. */
 int wadg_kernel_in_use(wadg_ctx ctx, int32_t rhs, int32_t fp32, int32_t* kernel);
 
 /* Static description of a status code; never NULL. */

@@ -16,19 +16,21 @@ LIB = os.path.join(PKG, "libwadg.so")
 DEMO = os.path.join(PKG, "abi_demo")
 
 SOURCES = ["reference.cpp", "stage_kernel.hip", "resident_kernel.hip", "split_kernel.hip",
-           "pipe_kernel.hip",
+           "quarter_kernel.hip", "pipe_kernel.hip",
            "adjoint_kernel.hip",
            "norms_kernel.hip", "l2_kernel.hip", "convert_kernel.hip", "parareal_kernel.hip", "launch.hip",
            "api.hip", "api_adjoint.hip", "api_batch.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-# Per-source flags.  The pipelined kernel loops over work items with every
-# operator entry a compile-time constant; machine-level loop-invariant code
-# motion would keep all of them in scalar registers across the loop and
-# spill most, so it is switched off for that file (the constants are then
-# rebuilt where they are used, as in the kernels without a loop).
-SOURCE_FLAGS = {"pipe_kernel.hip": ["-mllvm", "-disable-machine-licm"]}
+# Per-source flags.  The pipelined kernel loops over work items, and the
+# one-launch sweep over stages, with every operator entry a compile-time
+# constant; machine-level loop-invariant code motion would keep all of them
+# in scalar registers across the loop and spill most, so it is switched off
+# for those files (the constants are then rebuilt where they are used, as in
+# the kernels without a loop).
+SOURCE_FLAGS = {f: ["-mllvm", "-disable-machine-licm"]
+                for f in ("pipe_kernel.hip", "quarter_kernel.hip")}
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",

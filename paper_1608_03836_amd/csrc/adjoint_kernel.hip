@@ -24,7 +24,7 @@
 // One workgroup per (slice, 64-element group), two waves: wave 0 the
 // pressure field (weights c2_scale c^2/J) and the sensitivity term, wave 1
 // the two velocity fields (weights 1/J).  One partial-sum slot per
-// workgroup, updated by that workgroup only: deterministic, no atomics.
+// 16 elements, updated by one workgroup only: deterministic, no atomics.
 
 #include <hip/hip_runtime.h>
 
@@ -104,9 +104,8 @@ __global__ __launch_bounds__(2 * kWave) void adjoint_mass_kernel(const AdjMass a
   }
   if (wave == 0) {
     if (!active) dot = 0.0;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) dot += __shfl_xor(dot, off, 64);
-    if (lane == 0) a.part[w] += dot;
+    dot = sum16(dot);
+    if (lane % 16 == 0) a.part[4 * w + lane / 16] += dot;
   }
 }
 

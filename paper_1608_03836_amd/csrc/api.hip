@@ -333,12 +333,17 @@ int wadg_integrate(wadg_ctx ctx, double* Q, double* work, int32_t S, double dt, 
   if (nsteps == 0) return WADG_OK;
   DeviceGuard guard(ctx->device);
   if (!guard.ok) return fail(WADG_E_DEVICE, "cannot select the context's device");
+  wadg::StageParams p = base_params(ctx, S);
+  p.dt = dt;
+  if (one_launch_sweep(ctx, false, S)) {
+    int e = launch_sweep(ctx, Q, Q, p, nsteps, false, stream);
+    if (e) return hip_fail((hipError_t)e, "sweep kernel launch");
+    return WADG_OK;
+  }
   double* res = work;
   double* other = work + n;
   double* cur = Q;
-  wadg::StageParams p = base_params(ctx, S);
   p.res = res;
-  p.dt = dt;
   for (int stp = 0; stp < nsteps; ++stp)
     for (int i = 0; i < 5; ++i) {
       p.Qin = cur;
@@ -378,16 +383,21 @@ int wadg_integrate_fp32(wadg_ctx ctx, double* Q, void* work, int32_t S, double d
   if (nsteps == 0) return WADG_OK;
   DeviceGuard guard(ctx->device);
   if (!guard.ok) return fail(WADG_E_DEVICE, "cannot select the context's device");
+  wadg::StageParams p = base_params(ctx, S);
+  p.vol = ctx->d_vol32;
+  p.face = ctx->d_face32;
+  p.dt = dt;
+  if (one_launch_sweep(ctx, true, S)) {
+    int e = launch_sweep(ctx, Q, Q, p, nsteps, true, stream);
+    if (e) return hip_fail((hipError_t)e, "sweep kernel launch");
+    return WADG_OK;
+  }
   float* q0 = static_cast<float*>(work);
   float* q1 = q0 + n;
   float* res = q1 + n;
   int e = wadg::launch_to_fp32(Q, q0, n, stream);
   if (e) return hip_fail((hipError_t)e, "conversion kernel launch");
-  wadg::StageParams p = base_params(ctx, S);
-  p.vol = ctx->d_vol32;
-  p.face = ctx->d_face32;
   p.res = res;
-  p.dt = dt;
   float* cur = q0;
   for (int stp = 0; stp < nsteps; ++stp)
     for (int i = 0; i < 5; ++i) {

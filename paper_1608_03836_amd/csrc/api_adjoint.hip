@@ -17,11 +17,12 @@ namespace {
 // Adjoint workspace: two sets of the 5 stage residuals of every step of one
 // slice (one being recomputed while the other is read), two alternating
 // stage states, ybar, rbar, two alternating z (one slice each), then the
-// per-workgroup sensitivity partials.  (wadg_forward_checkpoints uses the
-// first five slices of it.)
+// sensitivity partials, four per element group.  (wadg_forward_checkpoints
+// uses the first five slices of it.)
 size_t adjoint_bytes(wadg_ctx ctx, int32_t nsteps) {
   const size_t n1 = ctx->slice_doubles();
-  return (10 * (size_t)nsteps + 6) * n1 * sizeof(double) + (size_t)ctx->groups() * sizeof(double);
+  return (10 * (size_t)nsteps + 6) * n1 * sizeof(double) +
+         (size_t)ctx->groups() * 4 * sizeof(double);
 }
 
 // One slice recomputed from its start state chk_s, keeping every stage
@@ -92,8 +93,16 @@ int wadg_forward_checkpoints(wadg_ctx ctx, double* chk, void* work, int32_t S, d
   if (!guard.ok) return fail(WADG_E_DEVICE, "cannot select the context's device");
   double* w = static_cast<double*>(work);
   double *t0 = w, *t1 = w + n1, *res = w + 2 * n1, *t2 = w + 3 * n1;
+  const bool one_launch = one_launch_sweep(ctx, false, 1);
   for (int s = 0; s < S; ++s) {
     const double* cur = chk + s * n1;
+    if (one_launch) {
+      wadg::StageParams p = base_params(ctx, 1);
+      p.dt = dt;
+      int e = launch_sweep(ctx, cur, chk + (s + 1) * n1, p, nsteps, false, stream);
+      if (e) return hip_fail((hipError_t)e, "sweep kernel launch");
+      continue;
+    }
     for (int m = 0; m < nsteps; ++m) {
       double* out = m == nsteps - 1 ? chk + (s + 1) * n1 : (m % 2 == 0 ? t2 : t0 + 4 * n1);
       int st = one_step(ctx, cur, out, t0, t1, res, dt, stream);
@@ -134,7 +143,7 @@ int wadg_adjoint(wadg_ctx ctx, const double* chk, const double* seed, double* gr
   // first stage of each slice (its residuals are recomputed just before)
   // and the last (no next stage in the slice).
   const bool fused = kernel_path(ctx, false, wadg::kApplyA, 1) == WADG_KERNEL_SPLIT;
-  const int G = ctx->groups();
+  const int G = 4 * ctx->groups();
   WADG_HIP(hipMemsetAsync(part, 0, (size_t)G * sizeof(double), hs));
   WADG_HIP(hipMemcpyAsync(yb, seed, sb, hipMemcpyDeviceToDevice, hs));
 

@@ -28,7 +28,8 @@ const double kRkB[5] = {1432997174477.0 / 9575080441755.0,
 // the geometry fits in LDS, else the split-work kernel; the adjoint's
 // apply-A launches take the split-work kernel (the resident kernel has no
 // apply-A mode, so an explicit RESIDENT or STREAMED choice runs them
-// streamed).
+// streamed).  Automatic launches of few elements take the quarter kernel
+// instead of any of these (takes_quarter).
 int kernel_path(wadg_ctx c, bool fp32, int mode, int32_t S) {
   if (mode == wadg::kStage && (c->kernel == WADG_KERNEL_PIPE || c->kernel == WADG_KERNEL_AUTO) &&
       S >= kPipeMinSlices && wadg::pipe_supported(c->N, c->nq1, fp32))
@@ -46,15 +47,43 @@ int kernel_path(wadg_ctx c, bool fp32, int mode, int32_t S) {
   return WADG_KERNEL_SPLIT;
 }
 
+namespace {
+
+// Whether an automatic launch over `sets` sets of 16 elements (all slices)
+// takes the quarter kernel: up to about as many sets as fill the CUs once.
+// Its launch takes the time of one short item, but each workgroup reads its
+// own copy of the geometry and exchanges every intermediate through LDS, so
+// it loses where several sets queue on a CU.  Measured on MI355X (256 CUs),
+// one stage launch against the kernel of kernel_path, FP64: N = 3, nq1 = 5:
+// 8.3 -> 5.8 us at 64 sets, 9.4 -> 6.9 at 256, 9.6 -> 8.6 at 384, 10.5 ->
+// 10.2 at 576, 11.7 -> 12.1 at 1024; N = 3, nq1 = 6: 12.2 -> 11.7 at 384,
+// 12.0 -> 12.8 at 484; N = 1: 5.0 -> 4.7 at 384, 4.8 -> 5.0 at 484; N = 4,
+// nq1 = 6: 12.7 -> 9.0 at 64, 15.8 -> 13.9 at 384, 14.8 -> 16.0 at 576.
+// FP32 items are half the bytes and registers: N = 3: 6.7 -> 4.8 at 64, 9.3
+// -> 8.5 at 1024; N = 2: 5.4 -> 4.9 at 484, 6.33 -> 6.39 at 1024.
+bool takes_quarter(wadg_ctx c, bool fp32, int64_t sets) {
+  if (c->kernel != WADG_KERNEL_AUTO) return false;
+  const int64_t cus = c->cus;
+  return sets <= (!fp32 ? cus * 3 / 2 : c->N >= 3 ? cus * 4 : cus * 2);
+}
+
+int64_t sets_of(wadg_ctx c, int32_t S) { return (int64_t)((c->K + 15) / 16) * S; }
+
+}  // namespace
+
 int launch_stage(wadg_ctx c, int mode, bool fp32, const wadg::StageParams& p0, void* stream) {
   const int path = kernel_path(c, fp32, mode, p0.S);
-  if (path == WADG_KERNEL_PIPE)
+  const bool quarter = takes_quarter(c, fp32, sets_of(c, p0.S));
+  if (path == WADG_KERNEL_PIPE && !quarter)
     return fp32 ? wadg::launch_stage_pipe_fp32(c->N, c->nq1, p0, c->cus, stream)
                 : wadg::launch_stage_pipe(c->N, c->nq1, p0, c->cus, stream);
   // alternate the item order from one launch to the next (item_of)
   wadg::StageParams p = p0;
   c->order_flip ^= 1;
   p.reverse = (int32_t)c->order_flip;
+  if (quarter)
+    return fp32 ? wadg::launch_stage_quarter_fp32(c->N, c->nq1, p, stream)
+                : wadg::launch_stage_quarter(c->N, c->nq1, mode, p, stream);
   if (path == WADG_KERNEL_SPLIT)
     return fp32 ? wadg::launch_stage_split_fp32(c->N, c->nq1, p, stream)
                 : wadg::launch_stage_split(c->N, c->nq1, mode, p, stream);
@@ -72,7 +101,38 @@ int launch_stage_pair(wadg_ctx c, int mode_a, const wadg::StageParams& a0,
   wadg::StageParams a = a0, b = b0;
   c->order_flip ^= 1;
   a.reverse = b.reverse = (int32_t)c->order_flip;
+  if (takes_quarter(c, false, sets_of(c, a0.S) + sets_of(c, b0.S)))
+    return wadg::launch_stage_quarter_pair(c->N, c->nq1, mode_a, a, b, stream);
   return wadg::launch_stage_pair(c->N, c->nq1, mode_a, a, b, stream);
+}
+
+// One launch for the whole sweep where a slice's mesh fits in one workgroup
+// (quarter_sweep_kernel): always for one or two sets of 16 elements; for
+// three, where N >= 3 or there are few slices; for four (whose workgroups
+// are held to 128 registers per lane, one per CU), where there are few.
+// Otherwise many slices fill the chip better from the stage kernels.
+// Measured per stage on MI355X (256 CUs), the stage launches against this
+// one, FP64, N = 3, nq1 = 5: 16 elements, 1 slice 7.9 -> 2.6 us, 4096 slices
+// 61.6 -> 19.0; 25 elements, 1 slice 8.0 -> 3.4, 4096 slices 67 -> 52; 36
+// elements, 2048 slices 35.2 -> 35.4; 64 elements, 512 slices 15.5 -> 13.7,
+// 2048 slices 36.7 -> 53.8.  N = 1, nq1 = 3, 36 elements, 4096 slices: 19.9
+// -> 27.4; N = 2, nq1 = 5: 46.5 -> 53.2.
+bool one_launch_sweep(wadg_ctx c, bool fp32, int32_t S) {
+  if (c->kernel != WADG_KERNEL_AUTO ||
+      c->K > wadg::quarter_sweep_elements(c->N, c->nq1, fp32))
+    return false;
+  const int sets = (c->K + 15) / 16;
+  return sets <= 2 || (sets == 3 && (c->N >= 3 || S <= 4 * c->cus)) || S <= 2 * c->cus;
+}
+
+int launch_sweep(wadg_ctx c, const double* Qin, double* Qout, const wadg::StageParams& p, int32_t nsteps, bool fp32,
+                 void* stream) {
+  wadg::SweepCoefs rk;
+  for (int i = 0; i < 5; ++i) {
+    rk.A[i] = kRkA[i];
+    rk.B[i] = kRkB[i];
+  }
+  return wadg::launch_sweep_quarter(c->N, c->nq1, Qin, Qout, p, rk, nsteps, fp32, stream);
 }
 
 wadg::StageParams base_params(wadg_ctx c, int32_t S) {

@@ -244,8 +244,8 @@ __device__ __forceinline__ double apply_a_mass_field(const StageScalars<double>&
 // One work item -- a 64-element group of one slice -- over the four waves of
 // the workgroup.  B: the item's resources; k: the stage's scalars; active:
 // this lane holds an element; tq, xf, xm: the workgroup's LDS (Split<>);
-// am, part: the fused apply-A + mass mode's scalars and this item's slot in
-// am.part.
+// am, part: the fused apply-A + mass mode's scalars and this item's index in
+// am.part (four slots per item).
 template <typename R, int N, int NQ, int MODE>
 __device__ __forceinline__ void split_item(const SplitBufs& B, const StageScalars<R>& k,
                                            bool active, R* tq, R* xf, R* xm,
@@ -330,9 +330,8 @@ __device__ __forceinline__ void split_item(const SplitBufs& B, const StageScalar
       if constexpr (MODE == kApplyAMass) {
         double dot = apply_a_mass_field<N, NQ>(k, B, am, 0, kb, active, resv, dq, w);
         if (!active) dot = 0.0;
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) dot += __shfl_xor(dot, off, 64);
-        if (lane == 0) am.part[part] += dot;
+        dot = sum16(dot);
+        if (lane % 16 == 0) am.part[4 * part + lane / 16] += dot;
       } else {
         finish_field<R, NP, MODE>(k, B.qout, B.resw, P, 0, kb, active, resv, dq);
       }

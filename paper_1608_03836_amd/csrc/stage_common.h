@@ -155,11 +155,14 @@ __device__ __forceinline__ void gather_trace(rsrc_t qslice, const NbrOffsets& o,
 
 // Pressure volume term, quadrature column i:
 //   bp += sum_j w J (l_r (Jr_x u + Jr_y v) + l_s (Js_x u + Js_y v))
-// with g[0..3][j] = W ys, -W xs, -W yr, W xr at point (i, j).
-template <typename R, int N, int NQ, typename FU, typename FV>
-__device__ __forceinline__ void pressure_volume_column(int i, const FU& U, const FV& V,
-                                                       const R (&g)[4][NQ],
-                                                       R (&bp)[(N + 1) * (N + 1)]) {
+// with g[0..3][j] = W ys, -W xs, -W yr, W xr at point (i, j).  The column's
+// sums over its points j (cr, cs per node row; vi = row i of V) and their
+// addition to the load vector are separate, so that different waves may do
+// them.
+template <typename R, int N, int NQ, bool PIN = false, typename FU, typename FV>
+__device__ __forceinline__ void pressure_column_sums(const R (&vi)[N + 1], const FU& U,
+                                                     const FV& V, const R (&g)[4][NQ],
+                                                     R (&cr)[N + 1], R (&cs)[N + 1]) {
   constexpr ct::Ops<R, N, NQ> T = ct::make_ops<R, N, NQ>();
   constexpr int NP1 = N + 1;
   R tu[NP1], tv[NP1];
@@ -168,13 +171,16 @@ __device__ __forceinline__ void pressure_volume_column(int i, const FU& U, const
     R su = R(0), sv = R(0);
 #pragma unroll
     for (int a = 0; a < NP1; ++a) {
-      su = mad(T.V[i][a], U(a + NP1 * bb), su);
-      sv = mad(T.V[i][a], V(a + NP1 * bb), sv);
+      su = mad(vi[a], U(a + NP1 * bb), su);
+      sv = mad(vi[a], V(a + NP1 * bb), sv);
     }
     tu[bb] = su;
     tv[bb] = sv;
   }
-  R cr[NP1], cs[NP1];
+  if constexpr (PIN) {
+    pin(tu);
+    pin(tv);
+  }
 #pragma unroll
   for (int bb = 0; bb < NP1; ++bb) cr[bb] = cs[bb] = R(0);
 #pragma unroll
@@ -193,18 +199,32 @@ __device__ __forceinline__ void pressure_volume_column(int i, const FU& U, const
       cs[bb] = mad(T.D[j][bb], Us, cs[bb]);
     }
   }
+}
+// Column i's sums of node row bb added to that row of the pressure load vector.
+template <typename R, int N, int NQ>
+__device__ __forceinline__ void pressure_column_add(int i, R cr, R cs, R* row) {
+  constexpr ct::Ops<R, N, NQ> T = ct::make_ops<R, N, NQ>();
 #pragma unroll
-  for (int bb = 0; bb < NP1; ++bb)
+  for (int a = 0; a <= N; ++a) row[a] = mad(T.D[i][a], cr, mad(T.V[i][a], cs, row[a]));
+}
+template <typename R, int N, int NQ, typename FU, typename FV>
+__device__ __forceinline__ void pressure_volume_column(int i, const FU& U, const FV& V,
+                                                       const R (&g)[4][NQ],
+                                                       R (&bp)[(N + 1) * (N + 1)]) {
+  constexpr ct::Ops<R, N, NQ> T = ct::make_ops<R, N, NQ>();
+  R cr[N + 1], cs[N + 1];
+  pressure_column_sums<R, N, NQ>(T.V[i], U, V, g, cr, cs);
 #pragma unroll
-    for (int a = 0; a < NP1; ++a)
-      bp[a + NP1 * bb] = mad(T.D[i][a], cr[bb], mad(T.V[i][a], cs[bb], bp[a + NP1 * bb]));
+  for (int bb = 0; bb <= N; ++bb) pressure_column_add<R, N, NQ>(i, cr[bb], cs[bb], bp + (N + 1) * bb);
 }
 
-// Velocity volume term, quadrature column i:  (bu, bv) -= sum_j w J l grad p.
-template <typename R, int N, int NQ, typename FP>
-__device__ __forceinline__ void velocity_volume_column(int i, const FP& P, const R (&g)[4][NQ],
-                                                       R (&bu)[(N + 1) * (N + 1)],
-                                                       R (&bv)[(N + 1) * (N + 1)]) {
+// Velocity volume term, quadrature column i:  (bu, bv) -= sum_j w J l grad p,
+// likewise as the column's sums (cx, cy per node row; vi, di = row i of V, D)
+// and their addition.
+template <typename R, int N, int NQ, bool PIN = false, typename FP>
+__device__ __forceinline__ void velocity_column_sums(const R (&vi)[N + 1], const R (&di)[N + 1],
+                                                     const FP& P, const R (&g)[4][NQ],
+                                                     R (&cx)[N + 1], R (&cy)[N + 1]) {
   constexpr ct::Ops<R, N, NQ> T = ct::make_ops<R, N, NQ>();
   constexpr int NP1 = N + 1;
   R td[NP1], tp[NP1];
@@ -214,13 +234,16 @@ __device__ __forceinline__ void velocity_volume_column(int i, const FP& P, const
 #pragma unroll
     for (int a = 0; a < NP1; ++a) {
       const R pa = P(a + NP1 * bb);
-      sd = mad(T.D[i][a], pa, sd);
-      sp = mad(T.V[i][a], pa, sp);
+      sd = mad(di[a], pa, sd);
+      sp = mad(vi[a], pa, sp);
     }
     td[bb] = sd;
     tp[bb] = sp;
   }
-  R cx[NP1], cy[NP1];
+  if constexpr (PIN) {
+    pin(td);
+    pin(tp);
+  }
 #pragma unroll
   for (int bb = 0; bb < NP1; ++bb) cx[bb] = cy[bb] = R(0);
 #pragma unroll
@@ -239,13 +262,25 @@ __device__ __forceinline__ void velocity_volume_column(int i, const FP& P, const
       cy[bb] = mad(T.V[j][bb], Gy, cy[bb]);
     }
   }
+}
+template <typename R, int N, int NQ>
+__device__ __forceinline__ void velocity_column_add(int i, R c, R* row) {
+  constexpr ct::Ops<R, N, NQ> T = ct::make_ops<R, N, NQ>();
 #pragma unroll
-  for (int bb = 0; bb < NP1; ++bb)
+  for (int a = 0; a <= N; ++a) row[a] = mad(-T.V[i][a], c, row[a]);
+}
+template <typename R, int N, int NQ, typename FP>
+__device__ __forceinline__ void velocity_volume_column(int i, const FP& P, const R (&g)[4][NQ],
+                                                       R (&bu)[(N + 1) * (N + 1)],
+                                                       R (&bv)[(N + 1) * (N + 1)]) {
+  constexpr ct::Ops<R, N, NQ> T = ct::make_ops<R, N, NQ>();
+  R cx[N + 1], cy[N + 1];
+  velocity_column_sums<R, N, NQ>(T.V[i], T.D[i], P, g, cx, cy);
 #pragma unroll
-    for (int a = 0; a < NP1; ++a) {
-      bu[a + NP1 * bb] = mad(-T.V[i][a], cx[bb], bu[a + NP1 * bb]);
-      bv[a + NP1 * bb] = mad(-T.V[i][a], cy[bb], bv[a + NP1 * bb]);
-    }
+  for (int bb = 0; bb <= N; ++bb) {
+    velocity_column_add<R, N, NQ>(i, cx[bb], bu + (N + 1) * bb);
+    velocity_column_add<R, N, NQ>(i, cy[bb], bv + (N + 1) * bb);
+  }
 }
 
 // Own and neighbour traces of p, u, v at face Gauss point j of face f.
@@ -432,6 +467,14 @@ __device__ __forceinline__ void finish_field(const StageScalars<R>& k, rsrc_t qo
   }
 }
 
+// Sum over the 16 lanes of a lane's quarter of the wave (a fixed tree; every
+// lane of the quarter gets it).
+__device__ __forceinline__ double sum16(double x) {
+#pragma unroll
+  for (int off = 8; off >= 1; off >>= 1) x += __shfl_xor(x, off, 64);
+  return x;
+}
+
 // Workgroup -> logical work index, XCD-aware: workgroups are dealt to the 8
 // XCDs round-robin, so XCD x = bid % 8 receives the contiguous logical range
 // [x q8 + min(x, r8), ...) in launch order.
@@ -449,6 +492,21 @@ __device__ __forceinline__ int xcd_remap(int bid, int nb) {
 __device__ __forceinline__ int item_of(int bid, int nb, int reverse) {
   const int w = xcd_remap(bid, nb);
   return reverse ? nb - 1 - w : w;
+}
+
+// Slice and element group of work item w in the schedule's order: tiles of
+// Be element groups x Bs slices, slice-major inside a tile, over S slices of
+// nEG groups.
+__device__ __forceinline__ void item_coords(int w, int nEG, int S, int Be, int Bs, int& s,
+                                            int& eg) {
+  const int sb = w / (Bs * nEG);
+  const int r = w - sb * Bs * nEG;
+  const int bs = min(Bs, S - sb * Bs);
+  const int eb = r / (Be * bs);
+  const int r2 = r - eb * Be * bs;
+  const int be = min(Be, nEG - eb * Be);
+  s = sb * Bs + r2 / be;
+  eg = eb * Be + r2 % be;
 }
 
 }  // namespace dev

@@ -60,13 +60,14 @@ void quadrature_points(const MeshIn& m, const RefOps& ops, double* xq, double* y
 // The adjoint mass step of the next reverse stage, fused into an apply-A
 // launch (mode kApplyAMass; split kernel, FP64).  With y the new ybar:
 //   rbar <- a_next rbar + b y;   z <- D Mtilde^{-1} rbar;
-//   part[group] += sum over pressure values of rbar (r - a r_prev).
+//   part[4 group + h] += sum over the pressure values of the group's elements
+//                        16 h .. 16 h + 15 of rbar (r - a r_prev).
 struct AdjMassParams {
   double* rbar;           // one slice, read (unless a_next = 0) and written
   double* z;              // one slice, written; not the launch's Qin
   const double* r;        // stage residual r_i of the mass stage
   const double* r_prev;   // r_{i-1}; NULL when a = 0
-  double* part;           // [groups] sensitivity partials
+  double* part;           // [groups][4] sensitivity partials
   double a_next, b, a;
 };
 
@@ -119,6 +120,22 @@ int launch_stage_split_fp32(int N, int nq, const StageParams& p, void* stream);
 // items of launch b; each item as in its own launch.
 int launch_stage_pair(int N, int nq, int mode_a, const StageParams& a, const StageParams& b,
                       void* stream);
+// Small launches (quarter_kernel.hip): one workgroup per 16 elements of one
+// slice, each element over several lanes; every mode.
+int launch_stage_quarter(int N, int nq, int mode, const StageParams& p, void* stream);
+int launch_stage_quarter_fp32(int N, int nq, const StageParams& p, void* stream);
+int launch_stage_quarter_pair(int N, int nq, int mode_a, const StageParams& a,
+                              const StageParams& b, void* stream);
+// The whole sweep of every slice of a mesh of at most
+// quarter_sweep_elements(N, nq, fp32) elements in one launch, one workgroup
+// per slice: Qout = Qin (FP64; may be the same array) advanced by nsteps steps
+// of p.dt, in FP64 or (fp32; geometry of float) in FP32.
+struct SweepCoefs {
+  double A[5], B[5];
+};
+int quarter_sweep_elements(int N, int nq, bool fp32);
+int launch_sweep_quarter(int N, int nq, const double* Qin, double* Qout, const StageParams& p,
+                         const SweepCoefs& rk, int nsteps, bool fp32, void* stream);
 // Resident-geometry kernel: one workgroup per (element group, slice range)
 // with the group's geometry held in LDS; grid = nEG * ranges.  Only where
 // resident_supported(N, nq, fp32).
@@ -129,8 +146,9 @@ int launch_stage_resident(int N, int nq, int mode, const StageParams& p, int ran
 // Adjoint mass step, elementwise (one workgroup per (slice, element group)):
 //   rbar <- a rbar + b ybar   (rbar not read when a == 0)
 //   z    <- D Mtilde^-1 rbar  (WADG inverse per field, c2_scale on p)
-//   part[w] += sum over p entries of rbar * (r_i - a_i r_prev)   (r_prev not
-//            read when a_i == 0), w = slice * nEG + group, one slot per workgroup
+//   part[4 w + h] += sum over p entries of rbar * (r_i - a_i r_prev)   (r_prev
+//            not read when a_i == 0), w = slice * nEG + group, elements 16 h ..
+//            16 h + 15 of the group
 int launch_adjoint_mass(int N, int nq, const StageParams& p, double* rbar, const double* ybar,
                         double* z, const double* r_i, const double* r_prev, double a_next,
                         double b_i, double a_i, double* part, void* stream);
