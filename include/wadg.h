@@ -415,7 +415,7 @@ int wadg_set_schedule(wadg_ctx ctx, int32_t groups_per_tile, int32_t slices_per_
  *     slices; ignores wadg_set_schedule.  Its FP64 geometry fits for N <= 2,
  *     or N = 3 with nq1 <= 5; elsewhere a RESIDENT request falls back to
  *     the streamed kernel for that precision.
- *   WADG_KERNEL_PIPE: LSRK stages only (FP64 and FP32-bulk): one
+ *   WADG_KERNEL_PIPE: LSRK stages (FP64 and FP32-bulk): one
  *     512-thread workgroup per CU (two in FP32 where both fit in LDS) that
  *     owns one element group and a run of its slices, keeps the group's
  *     geometry on chip for the whole run, streams the next slice's input tile into LDS while
@@ -431,7 +431,8 @@ int wadg_set_schedule(wadg_ctx ctx, int32_t groups_per_tile, int32_t slices_per_
  *     non-temporal cache hint.
  *   WADG_KERNEL_AUTO (default): LSRK stages (FP64 and FP32) of two or more
  *     slices take the pipelined kernel where it fits, else the split
- *     kernel; right-hand-side launches the resident kernel where it fits,
+ *     kernel; right-hand-side launches, where the geometry fits on chip
+ *     (wadg_kernel_in_use: WADG_KERNEL_RESIDENT), the pipelined kernel too,
  *     else the split kernel -- the fastest measured on MI355X.  Launches of
  *     few elements (all slices together: up to 24 per CU in FP64, 32 to 64
  *     in FP32) take a kernel that spreads each element over several lanes,

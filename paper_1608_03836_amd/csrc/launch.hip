@@ -25,7 +25,8 @@ const double kRkB[5] = {1432997174477.0 / 9575080441755.0,
 // elements, N = 3, FP64 and FP32): LSRK stages of two or more slices take
 // the pipelined kernel where its LDS plan fits, else the split-work
 // kernel; right-hand-side launches take the resident-geometry kernel where
-// the geometry fits in LDS, else the split-work kernel; the adjoint's
+// the geometry fits in LDS (launch_stage runs them on the pipelined kernel,
+// which keeps it on chip as well), else the split-work kernel; the adjoint's
 // apply-A launches take the split-work kernel (the resident kernel has no
 // apply-A mode, so an explicit RESIDENT or STREAMED choice runs them
 // streamed).  Automatic launches of few elements take the quarter kernel
@@ -74,9 +75,18 @@ int64_t sets_of(wadg_ctx c, int32_t S) { return (int64_t)((c->K + 15) / 16) * S;
 int launch_stage(wadg_ctx c, int mode, bool fp32, const wadg::StageParams& p0, void* stream) {
   const int path = kernel_path(c, fp32, mode, p0.S);
   const bool quarter = takes_quarter(c, fp32, sets_of(c, p0.S));
-  if (path == WADG_KERNEL_PIPE && !quarter)
+  // An automatic right-hand side whose geometry fits on chip runs on the
+  // pipelined kernel, which holds it there too and overlaps one slice's loads
+  // and face terms with another's mass inverse.  Measured on MI355X against
+  // the resident kernel, bitwise the same: 128x128 elements, N = 3, nq1 = 5,
+  // 256 slices 1,178 -> 909 us, 2 slices 20.4 -> 16.6, 1 slice 18.5 -> 11.1;
+  // 81x81, N = 2, 24 slices 39.9 -> 30.7; 64x64, N = 1, 64 slices 28.4 ->
+  // 19.3 (never slower at any size measured).
+  const bool pipe_rhs = mode == wadg::kRhs && c->kernel == WADG_KERNEL_AUTO &&
+                        wadg::pipe_supported(c->N, c->nq1, false);
+  if ((path == WADG_KERNEL_PIPE || pipe_rhs) && !quarter)
     return fp32 ? wadg::launch_stage_pipe_fp32(c->N, c->nq1, p0, c->cus, stream)
-                : wadg::launch_stage_pipe(c->N, c->nq1, p0, c->cus, stream);
+                : wadg::launch_stage_pipe(c->N, c->nq1, mode, p0, c->cus, stream);
   // alternate the item order from one launch to the next (item_of)
   wadg::StageParams p = p0;
   c->order_flip ^= 1;

@@ -39,7 +39,7 @@
 //
 // A first stage (A = 0) requests no residual; the last stage of a step,
 // whose residual is never read again, is a kernel instance of its own that
-// stores none.  The batched kernel runs the same roles over a list of runs
+// stores none, and a right-hand side one that has no residual and no update.  The batched kernel runs the same roles over a list of runs
 // of many problems, and lets the copies of a packed mesh share one copy's
 // geometry.
 //
@@ -56,6 +56,10 @@ namespace wadg {
 namespace {
 
 using namespace dev;
+
+// What a launch computes: an LSRK stage, one whose residual is not stored
+// (the last of a step), or the right-hand side alone.
+enum Kind { kStep, kLastStep, kRight };
 
 template <typename R, int N, int NQ>
 struct Pipe {
@@ -268,7 +272,6 @@ struct PipeRun {
   // gvoff, gfoff: byte offsets of this lane's values in `vol` and `face`.
   int glane, gelems;
   unsigned gvoff, gfoff;
-  unsigned res_bytes;   // bytes of a residual tile written: 0 drops the stores
   size_t goff;   // g times the values of one tile
   // offset (in values) of the group's tile in slice s
   __device__ __forceinline__ size_t grp(int s) const { return (size_t)s * slice_vals + goff; }
@@ -420,10 +423,10 @@ __device__ __forceinline__ void pipe_volume_role(const PipeRun<R>& run, int lane
 // of item j - 1 from the handed-over load vector, with mass weights c^2/J
 // (times the c^2 scale; LDS) or 1/J (registers), the residual requested one
 // item ahead, and the item's input values of the field kept in registers
-// from the step before (the tile buffer is refilled meanwhile).  RD: the
-// residual is not stored (the last stage of a step); NT: the outputs are
-// stored with the non-temporal hint.
-template <typename R, int N, int NQ, int C, bool RD, bool NT, bool BATCH>
+// from the step before (the tile buffer is refilled meanwhile).  A
+// right-hand side is the mass inverse alone.  NT: the outputs are stored
+// with the non-temporal hint.
+template <typename R, int N, int NQ, int C, int KIND, bool NT, bool BATCH>
 __device__ __forceinline__ void pipe_inverse_role(const PipeRun<R>& run, const StageScalars<R>& k,
                                                   int lane, unsigned kb,
                                                   R (*tq)[Pipe<R, N, NQ>::tile_alloc],
@@ -446,7 +449,8 @@ __device__ __forceinline__ void pipe_inverse_role(const PipeRun<R>& run, const S
     for (int q = 0; q < NQ2; ++q) wq[q] = ldr<R>(vol, BATCH ? run.gvoff : kb, (5 * NQ2 + q) * KP);
   }
   R resv[NP], qv[NP];
-  load_res<R, NP, kStage>(k, make_rsrc(run.res + grp(s0), tile * sizeof(R)), C, kb, resv);
+  if constexpr (KIND != kRight)
+    load_res<R, NP, kStage>(k, make_rsrc(run.res + grp(s0), tile * sizeof(R)), C, kb, resv);
   if constexpr (C == 0) wait_vm_all();                       // metric rows in LDS
   __syncthreads();                                           // prologue done
   for (int it = 0; it <= nit; ++it) {
@@ -465,10 +469,20 @@ __device__ __forceinline__ void pipe_inverse_role(const PipeRun<R>& run, const S
         wadg_inverse_wide<R, N, NQ>(b, wq, dq);
       }
       const rsrc_t qo = make_rsrc(run.qout + grp(s), tile * sizeof(R));
-      const rsrc_t rw = make_rsrc(run.resw + grp(s), run.res_bytes);
       const bool active = e < (s == run.slast ? run.klast : run.kfull);
       auto Qv = [&](int n) { return qv[n - C * NP]; };
-      if constexpr (!RD) {
+      if constexpr (KIND == kRight) {
+        if (active) {
+#pragma unroll
+          for (int n = 0; n < NP; ++n) {
+            if constexpr (NT)
+              st_nt(qo, kb, (C * NP + n) * KP, dq[n]);
+            else
+              st(qo, kb, (C * NP + n) * KP, dq[n]);
+          }
+        }
+      } else if constexpr (KIND == kStep) {
+        const rsrc_t rw = make_rsrc(run.resw + grp(s), tile * sizeof(R));
         if constexpr (NT)
           finish_field_nt<R, NP>(k, qo, rw, Qv, C, kb, active, resv, dq);
         else
@@ -487,14 +501,14 @@ __device__ __forceinline__ void pipe_inverse_role(const PipeRun<R>& run, const S
       }
       // the next item's residual; in a first stage (A = 0) resv keeps the
       // zeros the prologue gave it (batches: only for real elements)
-      if (it < nit && k.A != R(0) && (!BATCH || lane < run.kact(s + 1))) {
+      if (KIND != kRight && it < nit && k.A != R(0) && (!BATCH || lane < run.kact(s + 1))) {
         const rsrc_t rn = make_rsrc(run.res + grp(s + 1), tile * sizeof(R));
 #pragma unroll
         for (int n = 0; n < NP; ++n)
           resv[n] = NT ? ldr_nt<R>(rn, kb, (C * NP + n) * KP) : ldr<R>(rn, kb, (C * NP + n) * KP);
       }
     }
-    if (it < nit) {
+    if (KIND != kRight && it < nit) {
       // item it's input values of this field, before its buffer is refilled
       const R* t = tq[it & 1];
 #pragma unroll
@@ -509,7 +523,7 @@ __device__ __forceinline__ void pipe_inverse_role(const PipeRun<R>& run, const S
 // arrays (Pipe<>).  Wave w runs on SIMD w mod 4: waves 0..2 the volume
 // terms of p, u, v (wave 2 also loads the tiles), waves 3, 5, 6 the mass
 // inverses and updates of p, u, v, waves 4 and 7 the faces 0, 1 and 2, 3.
-template <typename R, int N, int NQ, bool RD, bool NT, bool BATCH>
+template <typename R, int N, int NQ, int KIND, bool NT, bool BATCH>
 __device__ __forceinline__ void pipe_run(const PipeRun<R>& run, const StageScalars<R>& k,
                                          R (*tq)[Pipe<R, N, NQ>::tile_alloc], R* xm, R* xf,
                                          R* xb, R* xw) {
@@ -549,11 +563,11 @@ __device__ __forceinline__ void pipe_run(const PipeRun<R>& run, const StageScala
   } else if (wave == 2) {
     pipe_volume_role<R, N, NQ, 2, true, BATCH>(run, lane, tq, xm, xf, xb);
   } else if (wave == 3) {
-    pipe_inverse_role<R, N, NQ, 0, RD, NT, BATCH>(run, k, lane, kb, tq, xb, xw);
+    pipe_inverse_role<R, N, NQ, 0, KIND, NT, BATCH>(run, k, lane, kb, tq, xb, xw);
   } else if (wave == 5) {
-    pipe_inverse_role<R, N, NQ, 1, RD, NT, BATCH>(run, k, lane, kb, tq, xb, xw);
+    pipe_inverse_role<R, N, NQ, 1, KIND, NT, BATCH>(run, k, lane, kb, tq, xb, xw);
   } else if (wave == 6) {
-    pipe_inverse_role<R, N, NQ, 2, RD, NT, BATCH>(run, k, lane, kb, tq, xb, xw);
+    pipe_inverse_role<R, N, NQ, 2, KIND, NT, BATCH>(run, k, lane, kb, tq, xb, xw);
   } else if (wave == 4) {
     pipe_face_role<R, N, NQ, 0, 1, BATCH>(run, k, lane, kb, tq, xf);
   } else {
@@ -565,11 +579,11 @@ __device__ __forceinline__ void pipe_run(const PipeRun<R>& run, const StageScala
 
 // Workgroup b: element group g and slices [s0, s1) of one problem;
 // grid = nEG * chunks, chunk j of group g holds slices
-// [j S / chunks, (j + 1) S / chunks).  LSRK stage mode only; RD = p.res_dead
-// (the last stage of a step, a kernel of its own so that the other stages'
-// code is not shaped by the branch); NT: non-temporal stores (launches
-// whose state is far larger than the caches).
-template <typename R, int N, int NQ, bool RD, bool NT>
+// [j S / chunks, (j + 1) S / chunks).  KIND: kLastStep where p.res_dead (a
+// kernel of its own so that the other stages' code is not shaped by the
+// branch); NT: non-temporal stores (launches whose state is far larger than
+// the caches).
+template <typename R, int N, int NQ, int KIND, bool NT>
 __global__ __launch_bounds__(8 * kWave) void pipe_kernel(const StageParams p, int chunks) {
   using L = Pipe<R, N, NQ>;
   constexpr int NQ2 = L::NQ2;
@@ -608,8 +622,7 @@ __global__ __launch_bounds__(8 * kWave) void pipe_kernel(const StageParams p, in
   run.glane = 0;                          // (batches only)
   run.gelems = kWave;
   run.gvoff = run.gfoff = 0;
-  run.res_bytes = RD ? 0u : L::tile * sizeof(R);
-  pipe_run<R, N, NQ, RD, NT, false>(run, stage_scalars<R>(p), tq, xm, xf, xb, xw);
+  pipe_run<R, N, NQ, KIND, NT, false>(run, stage_scalars<R>(p), tq, xm, xf, xb, xw);
 }
 
 // Batched LSRK stage (FP64) over a list of runs of many independent
@@ -618,8 +631,8 @@ __global__ __launch_bounds__(8 * kWave) void pipe_kernel(const StageParams p, in
 // the list is laid out for the XCD each workgroup lands on).  The problem's
 // descriptor supplies the state offset, geometry groups and dt, and the
 // real element count of every virtual slice (unused copies of a packed
-// last slice are not written).  RD, NT as for pipe_kernel.
-template <int N, int NQ, bool RD, bool NT>
+// last slice are not written).  KIND, NT as for pipe_kernel.
+template <int N, int NQ, int KIND, bool NT>
 __global__ __launch_bounds__(8 * kWave) void batch_pipe_kernel(const BatchParams bp,
                                                                const int32_t* runs, int nruns) {
   using R = double;
@@ -670,7 +683,6 @@ __global__ __launch_bounds__(8 * kWave) void batch_pipe_kernel(const BatchParams
   run.kfull = pr.K;
   run.slast = pr.S - 1;
   run.klast = pr.klast;
-  run.res_bytes = RD ? 0u : L::tile * sizeof(R);
   StageScalars<R> k;
   k.tau_p = bp.tau_p;
   k.tau_u = bp.tau_u;
@@ -678,17 +690,17 @@ __global__ __launch_bounds__(8 * kWave) void batch_pipe_kernel(const BatchParams
   k.B = bp.rkB;
   k.dt = pr.dt;
   k.c2s = 1.0;
-  pipe_run<R, N, NQ, RD, NT, true>(run, k, tq, xm, xf, xb, xw);
+  pipe_run<R, N, NQ, KIND, NT, true>(run, k, tq, xm, xf, xb, xw);
 }
 
 namespace {
 
 // Non-temporal stores where a launch's state (Q_in, Q_out and the residual:
-// three times `bytes`, one array) is well beyond the 256 MB memory-side
+// `bytes` together) is well beyond the 256 MB memory-side
 // cache; below that the next launch may still find what this one wrote.
 // Measured on MI355X, 128x128 elements x 256 slices (4.8 GB): about 1 %
 // faster per launch in FP64 and FP32, results unchanged.
-bool nt_stores(int64_t bytes) { return 3 * bytes > (int64_t)512 << 20; }
+bool nt_stores(int64_t bytes) { return bytes > (int64_t)512 << 20; }
 
 // Slice runs per element group: enough workgroups to give every CU one
 // (grid = nEG * chunks), at most one per slice.
@@ -699,9 +711,9 @@ int pipe_chunks(int nEG, int S, int cus) {
   return c;
 }
 
-template <typename R, int N, int NQ>
-int launch_nq(const StageParams& p, int cus, void* stream) {
-  if constexpr (!Pipe<R, N, NQ>::fits) {
+template <typename R, int N, int NQ, int KIND>
+int launch_kind(const StageParams& p, int cus, void* stream) {
+  if constexpr (!Pipe<R, N, NQ>::fits || (KIND == kRight && sizeof(R) != sizeof(double))) {
     return (int)hipErrorInvalidValue;
   } else {
     // two workgroups per CU where two fit in LDS (16 waves of at most 128
@@ -711,38 +723,40 @@ int launch_nq(const StageParams& p, int cus, void* stream) {
     if ((int64_t)p.nEG * chunks >= (1LL << 31)) return (int)hipErrorInvalidValue;
     const dim3 grid(p.nEG * chunks), block(8 * kWave);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (nt_stores((int64_t)p.S * p.nEG * Pipe<R, N, NQ>::tile_bytes)) {
-      if (p.res_dead)
-        hipLaunchKernelGGL((pipe_kernel<R, N, NQ, true, true>), grid, block, 0, st, p, chunks);
-      else
-        hipLaunchKernelGGL((pipe_kernel<R, N, NQ, false, true>), grid, block, 0, st, p, chunks);
-    } else {
-      if (p.res_dead)
-        hipLaunchKernelGGL((pipe_kernel<R, N, NQ, true, false>), grid, block, 0, st, p, chunks);
-      else
-        hipLaunchKernelGGL((pipe_kernel<R, N, NQ, false, false>), grid, block, 0, st, p, chunks);
-    }
+    // (a right-hand side has two state arrays, a stage three)
+    const int64_t bytes = (int64_t)p.S * p.nEG * Pipe<R, N, NQ>::tile_bytes;
+    if (nt_stores((KIND == kRight ? 2 : 3) * bytes))
+      hipLaunchKernelGGL((pipe_kernel<R, N, NQ, KIND, true>), grid, block, 0, st, p, chunks);
+    else
+      hipLaunchKernelGGL((pipe_kernel<R, N, NQ, KIND, false>), grid, block, 0, st, p, chunks);
     return (int)hipGetLastError();
   }
 }
 
+template <typename R, int N, int NQ>
+int launch_nq(int mode, const StageParams& p, int cus, void* stream) {
+  if (mode == kRhs) return launch_kind<R, N, NQ, kRight>(p, cus, stream);
+  return p.res_dead ? launch_kind<R, N, NQ, kLastStep>(p, cus, stream)
+                    : launch_kind<R, N, NQ, kStep>(p, cus, stream);
+}
+
 template <typename R, int N>
-int launch_n(int nq, const StageParams& p, int cus, void* stream) {
+int launch_n(int nq, int mode, const StageParams& p, int cus, void* stream) {
   switch (nq - N) {
-    case 1: return launch_nq<R, N, N + 1>(p, cus, stream);
-    case 2: return launch_nq<R, N, N + 2>(p, cus, stream);
-    case 3: return launch_nq<R, N, N + 3>(p, cus, stream);
+    case 1: return launch_nq<R, N, N + 1>(mode, p, cus, stream);
+    case 2: return launch_nq<R, N, N + 2>(mode, p, cus, stream);
+    case 3: return launch_nq<R, N, N + 3>(mode, p, cus, stream);
     default: return (int)hipErrorInvalidValue;
   }
 }
 
 template <typename R>
-int launch_r(int N, int nq, const StageParams& p, int cus, void* stream) {
+int launch_r(int N, int nq, int mode, const StageParams& p, int cus, void* stream) {
   switch (N) {
-    case 1: return launch_n<R, 1>(nq, p, cus, stream);
-    case 2: return launch_n<R, 2>(nq, p, cus, stream);
-    case 3: return launch_n<R, 3>(nq, p, cus, stream);
-    case 4: return launch_n<R, 4>(nq, p, cus, stream);
+    case 1: return launch_n<R, 1>(nq, mode, p, cus, stream);
+    case 2: return launch_n<R, 2>(nq, mode, p, cus, stream);
+    case 3: return launch_n<R, 3>(nq, mode, p, cus, stream);
+    case 4: return launch_n<R, 4>(nq, mode, p, cus, stream);
     default: return (int)hipErrorInvalidValue;
   }
 }
@@ -778,18 +792,18 @@ int launch_batch_nq(const BatchParams& p, const int32_t* runs, int32_t nruns, vo
   } else {
     const dim3 grid(nruns), block(8 * kWave);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (nt_stores((int64_t)p.nitems * Pipe<double, N, NQ>::tile_bytes)) {
+    if (nt_stores(3 * (int64_t)p.nitems * Pipe<double, N, NQ>::tile_bytes)) {
       if (p.res_dead)
-        hipLaunchKernelGGL((batch_pipe_kernel<N, NQ, true, true>), grid, block, 0, st, p, runs, nruns);
+        hipLaunchKernelGGL((batch_pipe_kernel<N, NQ, kLastStep, true>), grid, block, 0, st, p, runs, nruns);
       else
-        hipLaunchKernelGGL((batch_pipe_kernel<N, NQ, false, true>), grid, block, 0, st, p, runs,
+        hipLaunchKernelGGL((batch_pipe_kernel<N, NQ, kStep, true>), grid, block, 0, st, p, runs,
                            nruns);
     } else {
       if (p.res_dead)
-        hipLaunchKernelGGL((batch_pipe_kernel<N, NQ, true, false>), grid, block, 0, st, p, runs,
+        hipLaunchKernelGGL((batch_pipe_kernel<N, NQ, kLastStep, false>), grid, block, 0, st, p, runs,
                            nruns);
       else
-        hipLaunchKernelGGL((batch_pipe_kernel<N, NQ, false, false>), grid, block, 0, st, p, runs,
+        hipLaunchKernelGGL((batch_pipe_kernel<N, NQ, kStep, false>), grid, block, 0, st, p, runs,
                            nruns);
     }
     return (int)hipGetLastError();
@@ -823,12 +837,13 @@ int launch_batch_pipe(int N, int nq, const BatchParams& p, const int32_t* runs, 
   }
 }
 
-int launch_stage_pipe(int N, int nq, const StageParams& p, int cus, void* stream) {
-  return launch_r<double>(N, nq, p, cus, stream);
+int launch_stage_pipe(int N, int nq, int mode, const StageParams& p, int cus, void* stream) {
+  if (mode != kStage && mode != kRhs) return (int)hipErrorInvalidValue;
+  return launch_r<double>(N, nq, mode, p, cus, stream);
 }
 
 int launch_stage_pipe_fp32(int N, int nq, const StageParams& p, int cus, void* stream) {
-  return launch_r<float>(N, nq, p, cus, stream);
+  return launch_r<float>(N, nq, kStage, p, cus, stream);
 }
 
 }  // namespace wadg

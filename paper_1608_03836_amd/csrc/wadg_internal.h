@@ -161,9 +161,10 @@ int launch_copy(const double* in, double* out, size_t n, void* stream);
 bool stage_supported(int N, int nq);
 // Persistent pipelined kernel (pipe_kernel.hip): one eight-wave workgroup
 // per (element group, slice run), grid = nEG * chunks with chunks chosen
-// from the CU count; LSRK stage mode only, where its LDS fits.
+// from the CU count; LSRK stages and (FP64) right-hand sides, where its LDS
+// fits.
 bool pipe_supported(int N, int nq, bool fp32);
-int launch_stage_pipe(int N, int nq, const StageParams& p, int cus, void* stream);
+int launch_stage_pipe(int N, int nq, int mode, const StageParams& p, int cus, void* stream);
 int launch_stage_pipe_fp32(int N, int nq, const StageParams& p, int cus, void* stream);
 
 // Batched stage over many independent problems (same N, nq, penalties):
