@@ -397,7 +397,9 @@ int wadg_l2_norms(wadg_ctx ctx, const double* A, const double* B, int32_t S, voi
  * XCD takes a contiguous range of tiles.  Successive stage launches of a
  * context walk this order in alternating directions, so that a launch
  * starts on the items the previous one wrote last (memory-side cache
- * reuse).  Results do not depend on the order (bitwise).  Defaults: 8, 0.
+ * reuse).  Results do not depend on the order (bitwise).  Defaults: 8, 0;
+ * where most elements' neighbours lie in far groups (a mesh numbered at
+ * random), 8 and an eighth of the slices until this is called.
  * Not thread-safe per context.  Returns WADG_E_INVALID for
  * groups_per_tile < 1 or slices_per_tile < 0. */
 int wadg_set_schedule(wadg_ctx ctx, int32_t groups_per_tile, int32_t slices_per_tile);

@@ -50,6 +50,15 @@ int check_mesh(const wadg_mesh* m) {
   return WADG_OK;
 }
 
+double scattered_share(const wadg_mesh* m) {
+  const int64_t G = ((int64_t)m->K + wadg::kWave - 1) / wadg::kWave;
+  int64_t far = 0;
+  for (int64_t k = 0; k < m->K; ++k)
+    for (int f = 0; f < 4; ++f)
+      far += (k / wadg::kWave) * 8 / G != (m->etoe[4 * k + f] / wadg::kWave) * 8 / G;
+  return (double)far / (4.0 * m->K);
+}
+
 void mesh_scales(const double* vol, const double* face, int K, int nq, const double* wq,
                  bool tiled, double* h_min, double* c2_max) {
   const int nqq = nq * nq;
@@ -205,6 +214,7 @@ int wadg_create(const wadg_mesh* mesh, int32_t device, wadg_ctx* out) {
 
   wadg_ctx c = new wadg_ctx_s();
   c->h_min = h_min;
+  c->scattered = scattered_share(mesh) > 0.5;
   c->c2_max = c2_max;
   c->device = dev;
   int cus = 0;

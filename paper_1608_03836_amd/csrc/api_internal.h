@@ -16,7 +16,8 @@ struct wadg_ctx_s {
   int N = 0, nq1 = 0, K = 0;
   double tau_p = 1.0, tau_u = 1.0;
   int tile_groups = 8;   // schedule: element groups per tile
-  int tile_slices = 0;   // slices per tile (0: all)
+  int tile_slices = -1;  // slices per tile (0: all; -1: by the mesh's numbering)
+  bool scattered = false;  // most neighbours lie in far element groups (scattered_share)
   int kernel = WADG_KERNEL_AUTO;
   int cus = 256;         // compute units of the device
   double c2_scale = 1.0; // multiplies c^2 (wadg_set_c2_scale)
@@ -87,6 +88,11 @@ inline double cfl_number(double dt, int N, double h_min, double c2_max) {
   return dt * std::sqrt(c2_max) * (N + 1) * (N + 1) / h_min;
 }
 int check_slices(wadg_ctx c, int32_t S);
+
+// Share of the faces of a mesh whose neighbour lies in another eighth of its
+// element groups: what each XCD would read from elsewhere if it owned a
+// contiguous eighth of the groups.
+double scattered_share(const wadg_mesh* m);
 
 inline wadg::MeshIn mesh_in(const wadg_mesh* m) {
   return wadg::MeshIn{m->N, m->nq1, m->K, m->x, m->y, m->etoe, m->etof, m->c2q};

@@ -594,12 +594,20 @@ __global__ __launch_bounds__(8 * kWave) void pipe_kernel(const StageParams p, in
   __shared__ __attribute__((aligned(16))) R xb[L::xb];
   __shared__ __attribute__((aligned(16))) R xw[L::wp];
 
-  // workgroup -> (group, slice run), XCD-aware: each XCD takes a
-  // contiguous range of groups, so most neighbour traces are read by
-  // workgroups of the same XCD
+  // workgroup -> (group, slice run), XCD-aware: each XCD takes a contiguous
+  // range of groups, so most neighbour traces are read by workgroups of the
+  // same XCD.  Where the mesh is numbered without regard to neighbours,
+  // every XCD reads every slice's traces from everywhere in it; each XCD
+  // then takes a contiguous range of the slice runs instead, and reads only
+  // its own slices.  Measured on MI355X, N = 3, nq1 = 5, 64x64 elements
+  // numbered at random x 64 slices: FP64 151 -> 114 us, FP32 126 -> 68; N =
+  // 2, 81x81 x 24 slices, FP32 55 -> 40.  Numbered by rows it gains or loses
+  // up to 5 % (64x64: 75.6 -> 74.0, FP32 38.1 -> 40.6; 32x32: 22.2 -> 22.9),
+  // so the line is drawn where most neighbours are far (scattered_share).
   const int w = xcd_remap(blockIdx.x, gridDim.x);
-  const int g = w / chunks, j = w - g * chunks;
-  if (g >= p.nEG) return;                 // whole workgroup: no barrier reached
+  const int g = p.scattered ? w % p.nEG : w / chunks;
+  const int j = p.scattered ? w / p.nEG : w - g * chunks;
+  if (g >= p.nEG || j >= chunks) return;  // whole workgroup: no barrier reached
   const int s0 = (int)((int64_t)j * p.S / chunks);
   const int s1 = (int)((int64_t)(j + 1) * p.S / chunks);
   if (s1 <= s0) return;

@@ -88,6 +88,7 @@ struct StageParams {
   double rkA, rkB, dt;
   double c2_scale;       // c^2 multiplier (pressure mass weights)
   int32_t reverse;       // nonzero: the work items in reverse order
+  int32_t scattered;     // nonzero: most neighbours lie in far element groups
   int32_t res_dead;      // nonzero (stage mode): the residual this stage writes is never
                          // read -- the last stage of a step, the next step starting with
                          // A = 0 -- so the kernel may drop its store
