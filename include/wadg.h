@@ -420,10 +420,11 @@ int wadg_set_schedule(wadg_ctx ctx, int32_t groups_per_tile, int32_t slices_per_
  *   WADG_KERNEL_PIPE: LSRK stages (FP64 and FP32-bulk): one
  *     512-thread workgroup per CU (two in FP32 where both fit in LDS) that
  *     owns one element group and a run of its slices, keeps the group's
- *     geometry on chip for the whole run, streams the next slice's input tile into LDS while
- *     computing the current one, and applies one slice's mass inverse and
- *     update while the next slice's volume and face terms are formed (a
- *     two-stage pipeline over the slices); ignores wadg_set_schedule.
+ *     geometry on chip for the whole run, streams the next slice's input
+ *     tile into LDS while computing the current one, and applies one
+ *     slice's mass inverse and update while the next slice's volume and
+ *     face terms are formed (a two-stage pipeline over the slices); ignores
+ *     wadg_set_schedule.
  *     Needs two input tiles, the metric planes, the face terms, the
  *     handed-over load vectors and the pressure mass weights in LDS (FP64:
  *     N <= 3 with nq1 <= N + 2; FP32: every N, nq1); launches of fewer than
@@ -435,8 +436,10 @@ int wadg_set_schedule(wadg_ctx ctx, int32_t groups_per_tile, int32_t slices_per_
  *     slices take the pipelined kernel where it fits, else the split
  *     kernel; right-hand-side launches, where the geometry fits on chip
  *     (wadg_kernel_in_use: WADG_KERNEL_RESIDENT), the pipelined kernel too,
- *     else the split kernel -- the fastest measured on MI355X.  Launches of
- *     few elements (all slices together: up to 24 per CU in FP64, 32 to 64
+ *     else the split kernel -- the fastest measured on MI355X.  In place of
+ *     the split kernel, FP64 stages and right-hand sides with enough slices
+ *     per workgroup run on a form of the pipelined kernel that reads the
+ *     geometry again for each slice.  Launches of few elements (all slices together: up to 24 per CU in FP64, 32 to 64
  *     in FP32) take a kernel that spreads each element over several lanes,
  *     and the sweep of a mesh of few elements (one workgroup: up to 64,
  *     fewer at high degree or with many slices) runs as one launch.

@@ -26,7 +26,9 @@ const double kRkB[5] = {1432997174477.0 / 9575080441755.0,
 // the pipelined kernel where its LDS plan fits, else the split-work
 // kernel; right-hand-side launches take the resident-geometry kernel where
 // the geometry fits in LDS (launch_stage runs them on the pipelined kernel,
-// which keeps it on chip as well), else the split-work kernel; the adjoint's
+// which keeps it on chip as well), else the split-work kernel (for long
+// enough slice runs launch_stage uses the pipelined kernel's form that
+// streams the geometry, takes_streamed_pipe); the adjoint's
 // apply-A launches take the split-work kernel (the resident kernel has no
 // apply-A mode, so an explicit RESIDENT or STREAMED choice runs them
 // streamed).  Automatic launches of few elements take the quarter kernel
@@ -68,6 +70,28 @@ bool takes_quarter(wadg_ctx c, bool fp32, int64_t sets) {
   return sets <= (!fp32 ? cus * 3 / 2 : c->N >= 3 ? cus * 4 : cus * 2);
 }
 
+// Whether an automatic FP64 stage or right-hand side whose geometry does not
+// fit on chip (N = 4; N = 3 with nq1 = 6) takes the pipelined kernel's form
+// that streams it, rather than the split kernel.  Its workgroups walk
+// ceil(S / chunks) slices and one step more to drain the pipeline, and a CU
+// runs the split kernel's items two at a time; a step takes about two thirds
+// of such a round's time, so the shorter sum decides (a run of one slice per
+// workgroup stays split).  Measured on MI355X (256 CUs), stage and
+// right-hand side, us, split -> pipelined: N = 4, nq1 = 6: 50x50 elements
+// and 32 slices (5 rounds, 7 steps) 72.5 -> 66.4, 64.9 -> 52.8; 128x128 and
+// 64 slices (64, 65) 875 -> 659, 752 -> 514; 50x50 and 12 (2, 3) 30.2 ->
+// 28.1; but 96x96 and 16 (9, 17) 126 -> 142; 50x50 and 6 (1, 2) 16.4 ->
+// 17.9; nq1 = 5, 50x50 and 32: 59 -> 46.8, 50 -> 37.8; nq1 = 7: 94 -> 77, 82
+// -> 64; N = 3, nq1 = 6, 64x64 and 64: 164 -> 112, 135 -> 86; 24x24 and 30
+// (2, 3) 24.3 -> 18.5.
+bool takes_streamed_pipe(wadg_ctx c, const wadg::StageParams& p) {
+  if (c->kernel != WADG_KERNEL_AUTO || wadg::pipe_supported(c->N, c->nq1, false)) return false;
+  const int64_t chunks = wadg::pipe_chunks(p.nEG, p.S, c->cus);
+  const int64_t steps = (p.S + chunks - 1) / chunks + 1;
+  const int64_t rounds = ((int64_t)p.nEG * p.S + c->cus - 1) / c->cus;
+  return 3 * rounds >= 2 * steps;
+}
+
 int64_t sets_of(wadg_ctx c, int32_t S) { return (int64_t)((c->K + 15) / 16) * S; }
 
 }  // namespace
@@ -84,7 +108,9 @@ int launch_stage(wadg_ctx c, int mode, bool fp32, const wadg::StageParams& p0, v
   // 19.3 (never slower at any size measured).
   const bool pipe_rhs = mode == wadg::kRhs && c->kernel == WADG_KERNEL_AUTO &&
                         wadg::pipe_supported(c->N, c->nq1, false);
-  if ((path == WADG_KERNEL_PIPE || pipe_rhs) && !quarter)
+  const bool streamed_pipe =
+      !fp32 && (mode == wadg::kStage || mode == wadg::kRhs) && takes_streamed_pipe(c, p0);
+  if ((path == WADG_KERNEL_PIPE || pipe_rhs || streamed_pipe) && !quarter)
     return fp32 ? wadg::launch_stage_pipe_fp32(c->N, c->nq1, p0, c->cus, stream)
                 : wadg::launch_stage_pipe(c->N, c->nq1, mode, p0, c->cus, stream);
   // alternate the item order from one launch to the next (item_of)

@@ -39,14 +39,25 @@
 //
 // A first stage (A = 0) requests no residual; the last stage of a step,
 // whose residual is never read again, is a kernel instance of its own that
-// stores none, and a right-hand side one that has no residual and no update.  The batched kernel runs the same roles over a list of runs
-// of many problems, and lets the copies of a packed mesh share one copy's
-// geometry.
+// stores none, and a right-hand side one that has no residual and no update.
+// The batched kernel runs the same roles over a list of runs of many
+// problems, and lets the copies of a packed mesh share one copy's geometry.
 //
 // LDS at N = 3, FP64: two input tiles (48 KB), the metric planes (50 KB),
 // face terms (24 KB), the handed-over load vectors (24 KB) and the pressure
 // mass weights (12.5 KB): 158.5 KB, one workgroup per CU with two waves per
-// SIMD.  Instantiated where this fits in the CU's 160 KB.
+// SIMD.
+//
+// Where that does not fit in the CU's 160 KB (FP64 at N = 4, and N = 3 with
+// nq1 = 6) the geometry is streamed from memory once per item, as the split
+// kernel does, but the rest stays as above: a ring of columns requested two
+// (metric terms) or three (mass weights) ahead of their use, the velocity
+// waves' two metric planes held in registers up to nq1 = 6, and the nodal
+// values read from LDS for each column to make room for them.  What bounds
+// it is the chain of a step's loads and products with two waves per SIMD: at N = 4, nq1 = 6 a step takes 9.5 us (streamed
+// geometry 100 KB per CU and step, 2.7 TB/s over the chip) against 14.5 us
+// for a round of split items.  Held weights or a loop over the columns
+// (63 KB of code instead of 81) were slower or did not fit the registers.
 
 #include <hip/hip_runtime.h>
 
@@ -76,8 +87,16 @@ struct Pipe {
   static constexpr unsigned xf = 4u * 3 * NP1 * kWave;         // face terms [4][3][NP1][64]
   static constexpr unsigned xb = 3u * NP * kWave;              // load vectors handed over [3][NP][64]
   static constexpr unsigned wp = NQ2 * kWave;                  // pressure mass weights [NQ2][64]
-  static constexpr size_t lds_bytes = (2 * tile_alloc + metric + xf + xb + wp) * sizeof(R);
-  static constexpr bool fits = lds_bytes <= 160u * 1024u;
+  static constexpr size_t all_bytes = (2 * tile_alloc + metric + xf + xb + wp) * sizeof(R);
+  static constexpr bool fits = all_bytes <= 160u * 1024u;
+  // Where it does not fit (FP64 at N = 4, and at N = 3 with nq1 = 6) the
+  // geometry is streamed: the volume waves read the quadrature columns'
+  // metric terms from memory, the inverse waves the mass weights, and LDS
+  // holds the tiles, face terms and load vectors only.
+  static constexpr bool lean = !fits;
+  static constexpr unsigned xm_alloc = lean ? 64 : metric, xw_alloc = lean ? 64 : wp;
+  static constexpr size_t lds_bytes = (2 * tile_alloc + xm_alloc + xf + xb + xw_alloc) * sizeof(R);
+  static_assert(lds_bytes <= 160u * 1024u, "the streamed form fits in LDS");
 };
 
 // Rows r = w, w + nw, ... < ROWS of 1 KB (64 lanes x 16 B) from global
@@ -243,6 +262,57 @@ __device__ __forceinline__ void wadg_inverse_wide(const R (&b)[(N + 1) * (N + 1)
       for (int a = 0; a < NP1; ++a) dq[a + NP1 * bb] = mad(T.P[a][i], c[i][bb], dq[a + NP1 * bb]);
 }
 
+// The mass inverse of wadg_inverse, the same operations in the same order,
+// with the weights of plane `wplane` (times c2s for the pressure, PRESSURE)
+// read from memory three quadrature columns ahead.
+template <typename R, int N, int NQ, bool PRESSURE>
+__device__ __forceinline__ void wadg_inverse_streamed(const R (&b)[(N + 1) * (N + 1)], rsrc_t vol,
+                                                      unsigned kb, R c2s,
+                                                      R (&dq)[(N + 1) * (N + 1)]) {
+  constexpr ct::Ops<R, N, NQ> T = ct::make_ops<R, N, NQ>();
+  constexpr int NP1 = N + 1;
+  constexpr unsigned KP = kWave * sizeof(R);
+  R w[4][NQ];
+  auto weights = [&](int i) {
+#pragma unroll
+    for (int j = 0; j < NQ; ++j)
+      w[i & 3][j] = ldr<R>(vol, kb, ((PRESSURE ? 4 : 5) * NQ * NQ + i + NQ * j) * KP);
+  };
+#pragma unroll
+  for (int i = 0; i < 3; ++i) weights(i);
+#pragma unroll
+  for (int n = 0; n < NP1 * NP1; ++n) dq[n] = R(0);
+#pragma unroll
+  for (int i = 0; i < NQ; ++i) {
+    order();
+    if (i + 3 < NQ) weights(i + 3);
+    order();
+    R t[NP1], c[NP1];
+#pragma unroll
+    for (int bb = 0; bb < NP1; ++bb) {
+      R acc = R(0);
+#pragma unroll
+      for (int a = 0; a < NP1; ++a) acc = mad(T.Vt[i][a], b[a + NP1 * bb], acc);
+      t[bb] = acc;
+      c[bb] = R(0);
+    }
+#pragma unroll
+    for (int j = 0; j < NQ; ++j) {
+      R rq = R(0);
+#pragma unroll
+      for (int bb = 0; bb < NP1; ++bb) rq = mad(T.Vt[j][bb], t[bb], rq);
+      rq *= PRESSURE ? w[i & 3][j] * c2s : w[i & 3][j];
+#pragma unroll
+      for (int bb = 0; bb < NP1; ++bb) c[bb] = mad(T.P[bb][j], rq, c[bb]);
+    }
+#pragma unroll
+    for (int bb = 0; bb < NP1; ++bb)
+#pragma unroll
+      for (int a = 0; a < NP1; ++a) dq[a + NP1 * bb] = mad(T.P[a][i], c[bb], dq[a + NP1 * bb]);
+    pin(dq);
+  }
+}
+
 // One workgroup's work: element group g of a state whose slice s starts at
 // qin + s slice_vals (likewise qout, res, resw), slices [s0, s0 + nit); the
 // group's geometry resources; the elements of the group's lanes that are
@@ -361,8 +431,42 @@ __device__ __forceinline__ void pipe_volume_role(const PipeRun<R>& run, int lane
   auto tile_in = [&](int s, R* dst) {
     if (!BATCH || row_lane_needed(lane, run.kact(s))) tile_to_lds<L::rows>(tile_src(s), dst, lane);
   };
+  constexpr unsigned KP = kWave * sizeof(R);
+  const unsigned kb = (unsigned)lane * sizeof(R);
   if constexpr (LOADER) tile_in(run.s0, tq[0]);
   wait_vm_all();                                             // metric rows (and tile) in LDS
+  // column i's metric terms of the planes the field uses; with streamed
+  // geometry, those of a velocity component (two planes) stay in registers
+  // up to NQ = 6
+  constexpr bool held = L::lean && C != 0 && NQ <= 6;
+  constexpr bool streamed = L::lean && !held;
+  R gc[3][4][NQ], gm[2][held ? NQ2 : 1];
+  if constexpr (held) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int q = 0; q < NQ2; ++q) gm[h][q] = ldr<R>(run.vol, kb, ((C - 1 + 2 * h) * NQ2 + q) * KP);
+  }
+  auto metric = [&](int i, R (&g)[4][NQ]) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int jj = 0; jj < NQ; ++jj)
+        if (C == 0 || q == C - 1 || q == C + 1) {
+          if constexpr (held)
+            g[q][jj] = gm[q == C - 1 ? 0 : 1][i + NQ * jj];
+          else if constexpr (L::lean)
+            g[q][jj] = ldr<R>(run.vol, kb, (q * NQ2 + i + NQ * jj) * KP);
+          else
+            g[q][jj] = xm[(q * NQ2 + i + NQ * jj) * kWave + (BATCH ? run.glane : lane)];
+        } else {
+          g[q][jj] = R(0);
+        }
+  };
+  if constexpr (streamed) {
+    metric(0, gc[0]);
+    metric(1, gc[1]);
+  }
   __syncthreads();                                           // prologue done
   for (int it = 0; it <= nit; ++it) {
     R b[NP];
@@ -371,37 +475,55 @@ __device__ __forceinline__ void pipe_volume_role(const PipeRun<R>& run, int lane
         if (it + 1 < nit) tile_in(run.s0 + it + 1, tq[(it + 1) & 1]);
       }
       const R* t = tq[it & 1];
-      // the nodal values the volume term reads, in registers for all of its
-      // columns: u and v (pressure), p (velocity)
-      R x0[NP], x1[C == 0 ? NP : 1];
+      // the nodal values the volume term reads: u and v (pressure), p
+      // (velocity); in registers for all of its columns, or where the
+      // geometry is streamed (whose next column takes those) read from LDS
+      // again for each
+      constexpr int c0 = C == 0 ? NP : 0;
+      R x0[L::lean ? 1 : NP], x1[C == 0 && !L::lean ? NP : 1];
+      if constexpr (!L::lean) {
 #pragma unroll
-      for (int n = 0; n < NP; ++n) {
-        x0[n] = t[((C == 0 ? NP : 0) + n) * kWave + lane];
-        if constexpr (C == 0) x1[n] = t[(2 * NP + n) * kWave + lane];
+        for (int n = 0; n < NP; ++n) {
+          x0[n] = t[(c0 + n) * kWave + lane];
+          if constexpr (C == 0) x1[n] = t[(2 * NP + n) * kWave + lane];
+        }
       }
-      auto X0 = [&](int n) { return x0[n]; };
-      auto X1 = [&](int n) { return x1[n]; };
+      auto X0 = [&](int n) {
+        if constexpr (L::lean)
+          return t[(c0 + n) * kWave + lane];
+        else
+          return x0[n];
+      };
+      auto X1 = [&](int n) {
+        if constexpr (L::lean)
+          return t[(2 * NP + n) * kWave + lane];
+        else
+          return x1[n];
+      };
 #pragma unroll
       for (int n = 0; n < NP; ++n) b[n] = R(0);
 #pragma unroll
       for (int i = 0; i < NQ; ++i) {
         // this column's metric terms, requested before its first products
-        // (which need only the nodal values) so that they arrive meanwhile
-        R gc[4][NQ];
+        // (which need only the nodal values) so that they arrive meanwhile;
+        // streamed, those two columns ahead (at the end the next item's first)
         order();
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-          for (int jj = 0; jj < NQ; ++jj)
-            if (C == 0 || q == C - 1 || q == C + 1)
-              gc[q][jj] = xm[(q * NQ2 + i + NQ * jj) * kWave + (BATCH ? run.glane : lane)];
-            else
-              gc[q][jj] = R(0);
+        R(&g)[4][NQ] = gc[streamed ? i % 3 : 0];
+        if constexpr (streamed) {
+          if (i + 2 < NQ) metric(i + 2, gc[(i + 2) % 3]);
+          order();
+        } else {
+          metric(i, g);
+        }
         if constexpr (C == 0)
-          pressure_volume_column<R, N, NQ>(i, X0, X1, gc, b);
+          pressure_volume_column<R, N, NQ>(i, X0, X1, g, b);
         else
-          velocity_component_column<R, N, NQ, C>(i, X0, gc, b);
+          velocity_component_column<R, N, NQ, C>(i, X0, g, b);
         pin(b);
+      }
+      if constexpr (streamed) {
+        metric(0, gc[0]);
+        metric(1, gc[1]);
       }
     }
     __syncthreads();                                         // face terms ready
@@ -439,8 +561,9 @@ __device__ __forceinline__ void pipe_inverse_role(const PipeRun<R>& run, const S
   const rsrc_t vol = run.vol;
   const int e = run.g * kWave + lane;
   auto grp = [&](int s) { return run.grp(s); };
-  R wq[C == 0 ? 1 : NQ2];
-  if constexpr (C == 0) {
+  R wq[C == 0 || L::lean ? 1 : NQ2];
+  if constexpr (L::lean) {
+  } else if constexpr (C == 0) {
 #pragma unroll
     for (int q = 0; q < NQ2; ++q)
       xw[q * kWave + lane] = ldr<R>(vol, BATCH ? run.gvoff : kb, (4 * NQ2 + q) * KP) * k.c2s;
@@ -460,7 +583,15 @@ __device__ __forceinline__ void pipe_inverse_role(const PipeRun<R>& run, const S
 #pragma unroll
       for (int n = 0; n < NP; ++n) b[n] = xb[(C * NP + n) * kWave + lane];
       R dq[NP];
-      if constexpr (C == 0) {
+      if constexpr (L::lean) {
+        wadg_inverse_streamed<R, N, NQ, C == 0>(b, vol, kb, k.c2s, dq);
+        // the item's input values again (its tile's buffer is being refilled)
+        if constexpr (KIND != kRight) {
+          const rsrc_t qi = make_rsrc(run.qin + grp(s), tile * sizeof(R));
+#pragma unroll
+          for (int n = 0; n < NP; ++n) qv[n] = ldr<R>(qi, kb, (C * NP + n) * KP);
+        }
+      } else if constexpr (C == 0) {
         R wl[NQ2];
 #pragma unroll
         for (int q = 0; q < NQ2; ++q) wl[q] = xw[q * kWave + lane];
@@ -508,7 +639,7 @@ __device__ __forceinline__ void pipe_inverse_role(const PipeRun<R>& run, const S
           resv[n] = NT ? ldr_nt<R>(rn, kb, (C * NP + n) * KP) : ldr<R>(rn, kb, (C * NP + n) * KP);
       }
     }
-    if (KIND != kRight && it < nit) {
+    if (KIND != kRight && !L::lean && it < nit) {
       // item it's input values of this field, before its buffer is refilled
       const R* t = tq[it & 1];
 #pragma unroll
@@ -535,7 +666,7 @@ __device__ __forceinline__ void pipe_run(const PipeRun<R>& run, const StageScala
 
   // prologue: metric planes 0..3 of the group into LDS by waves 0..3 (the
   // face waves gather their first traces meanwhile)
-  if (wave <= 3) {
+  if (!L::lean && wave <= 3) {
     const int w = wave;
     if (!BATCH || run.gelems > 0) {
       if (!BATCH || row_lane_needed(lane, run.gelems))
@@ -589,10 +720,10 @@ __global__ __launch_bounds__(8 * kWave) void pipe_kernel(const StageParams p, in
   constexpr int NQ2 = L::NQ2;
   constexpr unsigned KP = kWave * sizeof(R);
   __shared__ __attribute__((aligned(1024))) R tq[2][L::tile_alloc];
-  __shared__ __attribute__((aligned(16))) R xm[L::metric];
+  __shared__ __attribute__((aligned(16))) R xm[L::xm_alloc];
   __shared__ __attribute__((aligned(16))) R xf[L::xf];
   __shared__ __attribute__((aligned(16))) R xb[L::xb];
-  __shared__ __attribute__((aligned(16))) R xw[L::wp];
+  __shared__ __attribute__((aligned(16))) R xw[L::xw_alloc];
 
   // workgroup -> (group, slice run), XCD-aware: each XCD takes a contiguous
   // range of groups, so most neighbour traces are read by workgroups of the
@@ -648,10 +779,10 @@ __global__ __launch_bounds__(8 * kWave) void batch_pipe_kernel(const BatchParams
   constexpr int NQ2 = L::NQ2;
   constexpr unsigned KP = kWave * sizeof(R);
   __shared__ __attribute__((aligned(1024))) R tq[2][L::tile_alloc];
-  __shared__ __attribute__((aligned(16))) R xm[L::metric];
+  __shared__ __attribute__((aligned(16))) R xm[L::xm_alloc];
   __shared__ __attribute__((aligned(16))) R xf[L::xf];
   __shared__ __attribute__((aligned(16))) R xb[L::xb];
-  __shared__ __attribute__((aligned(16))) R xw[L::wp];
+  __shared__ __attribute__((aligned(16))) R xw[L::xw_alloc];
   const int r = blockIdx.x;
   if (r >= nruns || runs[4 * r] < 0) return;   // whole workgroup: no barrier reached
   const int pi = runs[4 * r], g = runs[4 * r + 1];
@@ -710,18 +841,9 @@ namespace {
 // faster per launch in FP64 and FP32, results unchanged.
 bool nt_stores(int64_t bytes) { return bytes > (int64_t)512 << 20; }
 
-// Slice runs per element group: enough workgroups to give every CU one
-// (grid = nEG * chunks), at most one per slice.
-int pipe_chunks(int nEG, int S, int cus) {
-  int c = cus / (nEG > 0 ? nEG : 1);
-  if (c < 1) c = 1;
-  if (c > S) c = S;
-  return c;
-}
-
 template <typename R, int N, int NQ, int KIND>
 int launch_kind(const StageParams& p, int cus, void* stream) {
-  if constexpr (!Pipe<R, N, NQ>::fits || (KIND == kRight && sizeof(R) != sizeof(double))) {
+  if constexpr (KIND == kRight && sizeof(R) != sizeof(double)) {
     return (int)hipErrorInvalidValue;
   } else {
     // two workgroups per CU where two fit in LDS (16 waves of at most 128
@@ -780,6 +902,11 @@ bool fits_n(int nq) {
 }
 
 }  // namespace
+
+int pipe_chunks(int nEG, int S, int cus) {
+  const int64_t c = cus / (nEG > 0 ? nEG : 1);
+  return (int)(c < 1 ? 1 : c > S ? S : c);
+}
 
 bool pipe_supported(int N, int nq, bool fp32) {
   switch (N) {

@@ -162,9 +162,12 @@ int launch_copy(const double* in, double* out, size_t n, void* stream);
 bool stage_supported(int N, int nq);
 // Persistent pipelined kernel (pipe_kernel.hip): one eight-wave workgroup
 // per (element group, slice run), grid = nEG * chunks with chunks chosen
-// from the CU count; LSRK stages and (FP64) right-hand sides, where its LDS
-// fits.
+// from the CU count; LSRK stages and (FP64) right-hand sides.  Where its
+// geometry does not fit in LDS (pipe_supported false) the launch streams it.
 bool pipe_supported(int N, int nq, bool fp32);
+// Slice runs per element group: enough workgroups to give every CU one, at
+// most one per slice.
+int pipe_chunks(int nEG, int S, int cus);
 int launch_stage_pipe(int N, int nq, int mode, const StageParams& p, int cus, void* stream);
 int launch_stage_pipe_fp32(int N, int nq, const StageParams& p, int cus, void* stream);
 
