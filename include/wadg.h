@@ -290,8 +290,9 @@ int wadg_adjoint(wadg_ctx ctx, const double* chk, const double* seed, double* gr
  *   workgroup per run with the group's geometry on chip; elements of unused
  *   copies in a last virtual slice are neither computed into the state nor
  *   written (their values in Q are unspecified).  0 returns to the item
- *   schedule of wadg_batch_set_schedule.  Default 16 where the kernel's LDS
- *   plan fits (N <= 3 with nq1 <= N + 2), else 0.  Returns
+ *   schedule of wadg_batch_set_schedule.  Default where the kernel's LDS
+ *   plan fits (N <= 3 with nq1 <= N + 2): the length, 1 to 64, whose runs
+ *   fill the CUs best; else 0.  Returns
  *   WADG_E_UNSUPPORTED for run_slices > 0 where it does not fit.
  * wadg_batch_set_schedule: item schedule (and run_slices = 0).  wg_per_cu
  *   0: one four-wave workgroup per work item (the split-work kernel, as

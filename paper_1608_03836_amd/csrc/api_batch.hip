@@ -6,6 +6,7 @@
 #include <array>
 #include <cmath>
 #include <cstring>
+#include <functional>
 #include <string>
 #include <vector>
 
@@ -41,9 +42,6 @@ struct wadg_batch_s {
 };
 
 namespace {
-
-// Default slices per run of the pipelined batch kernel.
-constexpr int kBatchRunSlices = 16;
 
 void free_batch(wadg_batch b) {
   if (!b) return;
@@ -101,49 +99,128 @@ int32_t last_slice_elements(const wadg_batch b, int i) {
   return (b->S[i] - (b->Sv[i] - 1) * b->pack[i]) * b->K[i];
 }
 
+constexpr int kXcds = 8;
+using Run = std::array<int32_t, 4>;                // problem, group, first slice, slices
+using RunLists = std::vector<std::vector<Run>>;    // per XCD, in the order it takes them
+
 // Runs of the pipelined kernel: for every problem and element group of its
 // virtual mesh, the virtual slices in which the group holds a real element
 // (all but, possibly, the last), cut into ceil(n / run_slices) runs of
-// nearly equal length.  Placement: workgroups are dealt to the eight XCDs
-// round-robin (block b on XCD b % 8), so the list is laid out per block.
-// Whole problems go to one XCD each (largest first, to the XCD with the
-// least work so far), so that the neighbour traces a group reads come from
-// tiles its own XCD has just loaded; each XCD then takes its runs longest
-// first (runs of equal length problem-major).  Blocks past the end of
-// their XCD's list get an empty run (problem -1).  Uploaded like the work
-// list.
-int batch_upload_runs(wadg_batch b) {
-  using Run = std::array<int32_t, 4>;
+// nearly equal length; each XCD takes its runs longest first (runs of equal
+// length problem-major).  The neighbour traces a group reads should come
+// from tiles its own XCD has just loaded, so with `whole` a problem goes to
+// one XCD as a whole (largest first, to the XCD with the least work so far);
+// otherwise the problems' runs (slice range by slice range, all groups of
+// each) are dealt out in eight contiguous shares of equal work.
+RunLists place_runs(const wadg_batch b, int run_slices, bool whole) {
   std::vector<std::vector<Run>> per(b->nprob);
   std::vector<int64_t> work(b->nprob, 0);
-  for (int i = 0; i < b->nprob; ++i)
+  int64_t total = 0;
+  for (int i = 0; i < b->nprob; ++i) {
     for (int g = 0; g < b->nEG[i]; ++g) {
       const int n = b->Sv[i] - (g * wadg::kWave >= last_slice_elements(b, i) ? 1 : 0);
-      const int c = (n + b->run_slices - 1) / b->run_slices;
+      const int c = (n + run_slices - 1) / run_slices;
       for (int j = 0; j < c; ++j) {
         const int s0 = (int)((int64_t)j * n / c), s1 = (int)((int64_t)(j + 1) * n / c);
         per[i].push_back({i, g, s0, s1 - s0});
       }
       work[i] += n;
     }
-  std::vector<int> order(b->nprob);
-  for (int i = 0; i < b->nprob; ++i) order[i] = i;
-  std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return work[x] > work[y]; });
-  constexpr int kXcds = 8;
-  std::vector<std::vector<Run>> xcd(kXcds);
-  int64_t load[kXcds] = {};
-  for (int i : order) {
-    int x = 0;
-    for (int y = 1; y < kXcds; ++y)
-      if (load[y] < load[x]) x = y;
-    load[x] += work[i];
-    xcd[x].insert(xcd[x].end(), per[i].begin(), per[i].end());
+    total += work[i];
   }
-  size_t longest = 0;
-  for (auto& l : xcd) {
+  RunLists xcd(kXcds);
+  if (whole) {
+    std::vector<int> order(b->nprob);
+    for (int i = 0; i < b->nprob; ++i) order[i] = i;
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return work[x] > work[y]; });
+    int64_t load[kXcds] = {};
+    for (int i : order) {
+      int x = 0;
+      for (int y = 1; y < kXcds; ++y)
+        if (load[y] < load[x]) x = y;
+      load[x] += work[i];
+      xcd[x].insert(xcd[x].end(), per[i].begin(), per[i].end());
+    }
+  } else {
+    int64_t done = 0;
+    for (auto& runs : per) {
+      std::stable_sort(runs.begin(), runs.end(),
+                       [](const Run& u, const Run& v) { return u[2] < v[2]; });
+      for (const Run& r : runs) {
+        xcd[std::min<int64_t>(kXcds - 1, done * kXcds / std::max<int64_t>(1, total))].push_back(r);
+        done += r[3];
+      }
+    }
+  }
+  for (auto& l : xcd)
     std::stable_sort(l.begin(), l.end(), [](const Run& u, const Run& v) { return u[3] > v[3]; });
-    longest = std::max(longest, l.size());
+  return xcd;
+}
+
+// When the last run ends, in items: each XCD's CUs take its runs in order,
+// one at a time, a run of n slices lasting n + 1 pipeline steps and a
+// prologue (geometry and first tile) of about one more.
+double runs_end(const RunLists& xcd, int cus) {
+  constexpr double kOverhead = 2.0;
+  double end = 0.0;
+  for (const auto& l : xcd) {
+    std::vector<double> h(std::max(1, cus / kXcds), 0.0);     // a heap, earliest free CU first
+    for (const Run& r : l) {
+      std::pop_heap(h.begin(), h.end(), std::greater<double>());
+      h.back() += r[3] + kOverhead;
+      end = std::max(end, h.back());
+      std::push_heap(h.begin(), h.end(), std::greater<double>());
+    }
   }
+  return end;
+}
+
+// The placement of runs of at most run_slices that ends first; dealing the
+// problems out has to gain a tenth, for the traces that then cross XCDs.
+RunLists best_placement(const wadg_batch b, int run_slices, double* end) {
+  RunLists whole = place_runs(b, run_slices, true), dealt = place_runs(b, run_slices, false);
+  const double ew = runs_end(whole, b->cus), ed = runs_end(dealt, b->cus);
+  *end = std::min(ew, ed / 0.9);
+  return ed < 0.9 * ew ? dealt : whole;
+}
+
+// Default slices per run: the length whose last run ends first, the longest
+// of equals.  Long runs pay the prologue and the pipeline's drain less often,
+// short ones fill the CUs of a small batch and even out the last wave.
+// Measured on MI355X per stage, N = 3, nq1 = 5, uneven problems of 4 to 256
+// elements and 8 to 128 slices, runs of 16 on whole problems against this
+// choice of length and placement: 3 problems 58 -> 9.9 us, 12 56.6 -> 19.3, 30
+// 99.7 -> 47.6, 60 125 -> 114, 120 164 -> 155, 250 417 -> 404.  Over 20
+// batches, N = 1..3, the choice was within 13 % of the best length tried, and
+// never slower than runs of 16 by more than 3 %.
+int default_run_slices(const wadg_batch b) {
+  int best = 1, last = 0;
+  double best_end = -1.0;
+  const int most = *std::max_element(b->Sv.begin(), b->Sv.end());
+  for (int L : {64, 48, 40, 32, 28, 24, 20, 16, 14, 12, 10, 8, 7, 6, 5, 4, 3, 2, 1}) {
+    L = std::min(L, most);
+    if (L == last) continue;
+    last = L;
+    // (short runs of many items only cost time, here and there)
+    if (L < 16 && b->items / L > 16 * (int64_t)b->cus) break;
+    double end;
+    best_placement(b, L, &end);
+    if (best_end < 0.0 || end < best_end) {
+      best_end = end;
+      best = L;
+    }
+  }
+  return best;
+}
+
+// The runs' list.  Workgroups are dealt to the eight XCDs round-robin (block
+// b on XCD b % 8), so it is laid out per block; blocks past the end of their
+// XCD's list get an empty run (problem -1).  Uploaded like the work list.
+int batch_upload_runs(wadg_batch b) {
+  double end;
+  const RunLists xcd = best_placement(b, b->run_slices, &end);
+  size_t longest = 0;
+  for (auto& l : xcd) longest = std::max(longest, l.size());
   std::vector<int32_t> r;
   r.reserve(longest * kXcds * 4);
   for (size_t j = 0; j < longest; ++j)
@@ -422,7 +499,7 @@ int wadg_batch_create(const wadg_mesh* meshes, int32_t nprob, const int32_t* S, 
   }
   int st = batch_upload_items(b);
   if (!st && wadg::batch_pipe_supported(N, nq)) {   // the default schedule
-    b->run_slices = kBatchRunSlices;
+    b->run_slices = default_run_slices(b);
     st = batch_upload_runs(b);
   }
   if (st) {
