@@ -330,6 +330,80 @@ int wadg_rhs(wadg_ctx ctx, const double* Q, double* dQdt, int32_t S, void* strea
   return WADG_OK;
 }
 
+namespace {
+
+// The sweeps of wadg_integrate and wadg_integrate_fp32 from the state src into
+// Q: in place (src == Q), or leaving src, which overlaps neither Q nor work.
+int sweep_from(wadg_ctx ctx, const double* src, double* Q, double* work, int32_t S, double dt,
+               int32_t nsteps, void* stream) {
+  const size_t n = ctx->state_doubles(S);
+  wadg::StageParams p = base_params(ctx, S);
+  p.dt = dt;
+  if (one_launch_sweep(ctx, false, S)) {
+    int e = launch_sweep(ctx, src, Q, p, nsteps, false, stream);
+    if (e) return hip_fail((hipError_t)e, "sweep kernel launch");
+    return WADG_OK;
+  }
+  double* other = work + n;
+  const double* cur = src;
+  p.res = work;
+  for (int64_t left = 5 * (int64_t)nsteps; left > 0; --left) {
+    const int i = (int)((5 - left % 5) % 5);                 // the stage of its step
+    // the two states in turn; from another state, so that the last is Q
+    double* out = src == Q ? (cur == Q ? other : Q) : (left % 2 ? Q : other);
+    p.Qin = cur;
+    p.Qout = out;
+    p.rkA = kRkA[i];
+    p.rkB = kRkB[i];
+    p.res_dead = i == 4;
+    int e = launch_stage(ctx, wadg::kStage, false, p, stream);
+    if (e) return hip_fail((hipError_t)e, "stage kernel launch");
+    cur = out;
+  }
+  if (cur != Q) {
+    int e = wadg::launch_copy(cur, Q, n, stream);
+    if (e) return hip_fail((hipError_t)e, "copy kernel launch");
+  }
+  return WADG_OK;
+}
+
+int sweep_fp32_from(wadg_ctx ctx, const double* src, double* Q, void* work, int32_t S, double dt,
+                    int32_t nsteps, void* stream) {
+  const size_t n = ctx->state_doubles(S);
+  wadg::StageParams p = base_params(ctx, S);
+  p.vol = ctx->d_vol32;
+  p.face = ctx->d_face32;
+  p.dt = dt;
+  if (one_launch_sweep(ctx, true, S)) {
+    int e = launch_sweep(ctx, src, Q, p, nsteps, true, stream);
+    if (e) return hip_fail((hipError_t)e, "sweep kernel launch");
+    return WADG_OK;
+  }
+  float* q0 = static_cast<float*>(work);
+  float* q1 = q0 + n;
+  float* res = q1 + n;
+  int e = wadg::launch_to_fp32(src, q0, n, stream);
+  if (e) return hip_fail((hipError_t)e, "conversion kernel launch");
+  p.res = res;
+  float* cur = q0;
+  for (int stp = 0; stp < nsteps; ++stp)
+    for (int i = 0; i < 5; ++i) {
+      p.Qin = cur;
+      p.Qout = (cur == q0) ? q1 : q0;
+      p.rkA = kRkA[i];
+      p.rkB = kRkB[i];
+      p.res_dead = i == 4;
+      e = launch_stage(ctx, wadg::kStage, true, p, stream);
+      if (e) return hip_fail((hipError_t)e, "stage kernel launch");
+      cur = static_cast<float*>(p.Qout);
+    }
+  e = wadg::launch_to_fp64(cur, Q, n, stream);
+  if (e) return hip_fail((hipError_t)e, "conversion kernel launch");
+  return WADG_OK;
+}
+
+}  // namespace
+
 int wadg_integrate(wadg_ctx ctx, double* Q, double* work, int32_t S, double dt, int32_t nsteps,
                    void* stream) {
   int st = check_slices(ctx, S);
@@ -343,33 +417,7 @@ int wadg_integrate(wadg_ctx ctx, double* Q, double* work, int32_t S, double dt, 
   if (nsteps == 0) return WADG_OK;
   DeviceGuard guard(ctx->device);
   if (!guard.ok) return fail(WADG_E_DEVICE, "cannot select the context's device");
-  wadg::StageParams p = base_params(ctx, S);
-  p.dt = dt;
-  if (one_launch_sweep(ctx, false, S)) {
-    int e = launch_sweep(ctx, Q, Q, p, nsteps, false, stream);
-    if (e) return hip_fail((hipError_t)e, "sweep kernel launch");
-    return WADG_OK;
-  }
-  double* res = work;
-  double* other = work + n;
-  double* cur = Q;
-  p.res = res;
-  for (int stp = 0; stp < nsteps; ++stp)
-    for (int i = 0; i < 5; ++i) {
-      p.Qin = cur;
-      p.Qout = (cur == Q) ? other : Q;
-      p.rkA = kRkA[i];
-      p.rkB = kRkB[i];
-      p.res_dead = i == 4;
-      int e = launch_stage(ctx, wadg::kStage, false, p, stream);
-      if (e) return hip_fail((hipError_t)e, "stage kernel launch");
-      cur = static_cast<double*>(p.Qout);
-    }
-  if (cur != Q) {
-    int e = wadg::launch_copy(cur, Q, n, stream);
-    if (e) return hip_fail((hipError_t)e, "copy kernel launch");
-  }
-  return WADG_OK;
+  return sweep_from(ctx, Q, Q, work, S, dt, nsteps, stream);
 }
 
 int wadg_workspace_bytes_fp32(wadg_ctx ctx, int32_t S, size_t* bytes) {
@@ -393,36 +441,7 @@ int wadg_integrate_fp32(wadg_ctx ctx, double* Q, void* work, int32_t S, double d
   if (nsteps == 0) return WADG_OK;
   DeviceGuard guard(ctx->device);
   if (!guard.ok) return fail(WADG_E_DEVICE, "cannot select the context's device");
-  wadg::StageParams p = base_params(ctx, S);
-  p.vol = ctx->d_vol32;
-  p.face = ctx->d_face32;
-  p.dt = dt;
-  if (one_launch_sweep(ctx, true, S)) {
-    int e = launch_sweep(ctx, Q, Q, p, nsteps, true, stream);
-    if (e) return hip_fail((hipError_t)e, "sweep kernel launch");
-    return WADG_OK;
-  }
-  float* q0 = static_cast<float*>(work);
-  float* q1 = q0 + n;
-  float* res = q1 + n;
-  int e = wadg::launch_to_fp32(Q, q0, n, stream);
-  if (e) return hip_fail((hipError_t)e, "conversion kernel launch");
-  p.res = res;
-  float* cur = q0;
-  for (int stp = 0; stp < nsteps; ++stp)
-    for (int i = 0; i < 5; ++i) {
-      p.Qin = cur;
-      p.Qout = (cur == q0) ? q1 : q0;
-      p.rkA = kRkA[i];
-      p.rkB = kRkB[i];
-      p.res_dead = i == 4;
-      e = launch_stage(ctx, wadg::kStage, true, p, stream);
-      if (e) return hip_fail((hipError_t)e, "stage kernel launch");
-      cur = static_cast<float*>(p.Qout);
-    }
-  e = wadg::launch_to_fp64(cur, Q, n, stream);
-  if (e) return hip_fail((hipError_t)e, "conversion kernel launch");
-  return WADG_OK;
+  return sweep_fp32_from(ctx, Q, Q, work, S, dt, nsteps, stream);
 }
 
 namespace {
@@ -462,6 +481,7 @@ int wadg_parareal(wadg_ctx ctx, const double* y0, double* U, void* work, int32_t
     return fail(WADG_E_INVALID, "coarse step dt * nsteps_fine / nsteps_coarse has CFL number " +
                                     std::to_string(nu_c) + " > " + std::to_string(WADG_CFL_MAX) +
                                     ": raise nsteps_coarse");
+  if (!(dtc > 0.0)) return fail(WADG_E_INVALID, "dt must be finite and > 0");
   const size_t n1 = ctx->slice_doubles();
   const size_t ubytes = (S + 1) * n1 * sizeof(double);
   const size_t wbytes = parareal_bytes(ctx, S, fine_fp32);
@@ -482,42 +502,50 @@ int wadg_parareal(wadg_ctx ctx, const double* y0, double* U, void* work, int32_t
   const int32_t tile = (int32_t)ctx->tile();
   const size_t sb = n1 * sizeof(double);
 
-  auto coarse = [&](double* q) { return wadg_integrate(ctx, q, cwork, 1, dtc, nsteps_coarse, stream); };
+  auto coarse = [&](const double* from, double* to) {
+    return sweep_from(ctx, from, to, cwork, 1, dtc, nsteps_coarse, stream);
+  };
   if (y0 != U) WADG_HIP(hipMemcpyAsync(U, y0, sb, hipMemcpyDeviceToDevice, hs));
   // coarse prediction U_{s+1}^0 = G(U_s^0), remembered as G(U_s^0)
-  for (int s = 0; s < S; ++s) {
-    WADG_HIP(hipMemcpyAsync(Gold + s * n1, U + s * n1, sb, hipMemcpyDeviceToDevice, hs));
-    if ((st = coarse(Gold + s * n1))) return st;
-    WADG_HIP(hipMemcpyAsync(U + (s + 1) * n1, Gold + s * n1, sb, hipMemcpyDeviceToDevice, hs));
-  }
+  for (int s = 0; s < S; ++s)
+    if ((st = coarse(U + s * n1, U + (s + 1) * n1))) return st;
+  WADG_HIP(hipMemcpyAsync(Gold, U + n1, (size_t)S * sb, hipMemcpyDeviceToDevice, hs));
   std::vector<double> out((size_t)S * 4);
   double change = INFINITY;
   int32_t it = 0;
   for (int k = 0; k < max_iter; ++k) {
-    // fine propagation of all slices at once: F_s = F(U_s^k)
-    WADG_HIP(hipMemcpyAsync(F, U, (size_t)S * sb, hipMemcpyDeviceToDevice, hs));
-    st = fine_fp32 ? wadg_integrate_fp32(ctx, F, fwork, S, dt, nsteps_fine, stream)
-                   : wadg_integrate(ctx, F, reinterpret_cast<double*>(fwork), S, dt, nsteps_fine,
-                                    stream);
+    // U_0 never changes, so iteration k leaves U_1..U_k as iteration k - 1
+    // made them, to the bit: their propagations would repeat Gold and F, the
+    // coarse one of slice k repeats Gold.  From iteration S on nothing
+    // changes, as iteration S's change of zero (over slice S - 1) reports.
+    // Measured on MI355X, 32x32 elements, N = 3, 16 slices, 17 coarse steps, two
+    // iterations: 27.0 -> 25.3 ms, with the copies around each sweep.
+    const int k0 = std::min(k, S - 1);
+    // fine propagation of all slices that changed at once: F_s = F(U_s^k)
+    st = fine_fp32 ? sweep_fp32_from(ctx, U + k0 * n1, F + k0 * n1, fwork, S - k0, dt, nsteps_fine,
+                                     stream)
+                   : sweep_from(ctx, U + k0 * n1, F + k0 * n1, reinterpret_cast<double*>(fwork),
+                                S - k0, dt, nsteps_fine, stream);
     if (st) return st;
     // serial coarse sweep with the correction update
-    for (int s = 0; s < S; ++s) {
-      WADG_HIP(hipMemcpyAsync(tmp, U + s * n1, sb, hipMemcpyDeviceToDevice, hs));
-      if ((st = coarse(tmp))) return st;
-      int e = wadg::launch_parareal_correct(tmp, F + s * n1, Gold + s * n1, U + (s + 1) * n1,
+    for (int s = k0; s < S; ++s) {
+      double* g = s == k0 ? Gold + s * n1 : tmp;
+      if (s > k0 && (st = coarse(U + s * n1, tmp))) return st;
+      int e = wadg::launch_parareal_correct(g, F + s * n1, Gold + s * n1, U + (s + 1) * n1,
                                             (int64_t)n1, tile, ctx->K,
                                             partials + (size_t)s * kNormBlocks * 4, kNormBlocks,
                                             stream);
       if (e) return hip_fail((hipError_t)e, "parareal correction launch");
     }
-    int e = wadg::launch_norms_final(partials, kNormBlocks, S, dout, stream);
+    int e = wadg::launch_norms_final(partials + (size_t)k0 * kNormBlocks * 4, kNormBlocks, S - k0,
+                                     dout, stream);
     if (e) return hip_fail((hipError_t)e, "reduction launch");
-    WADG_HIP(hipMemcpyAsync(out.data(), dout, out.size() * sizeof(double), hipMemcpyDeviceToHost,
-                            hs));
+    WADG_HIP(hipMemcpyAsync(out.data(), dout, (size_t)(S - k0) * 4 * sizeof(double),
+                            hipMemcpyDeviceToHost, hs));
     WADG_HIP(hipStreamSynchronize(hs));
     it = k + 1;
     change = 0.0;
-    for (int s = 0; s < S; ++s) {
+    for (int s = 0; s < S - k0; ++s) {
       if (out[4 * s + 3] != 0.0) {
         *iterations = it;
         *last_change = NAN;

@@ -6,7 +6,8 @@
 // the stored one, and the per-slice reductions of the change
 // ||U_{s+1}^{k+1} - U_{s+1}^k||^2, ||U_{s+1}^{k+1}||^2, max |change| and a
 // non-finite flag are written as block partials (fixed-order reduction, as
-// for the norms).  Padding lanes of the tiled layout are skipped.
+// for the norms).  Padding lanes of the tiled layout are skipped.  g may be
+// gold (a coarse value that has not changed).
 
 #include <hip/hip_runtime.h>
 
@@ -17,8 +18,8 @@ namespace wadg {
 constexpr int kCorrThreads = 256;
 
 __global__ __launch_bounds__(kCorrThreads) void parareal_correct_kernel(
-    const double* __restrict__ g, const double* __restrict__ f, double* __restrict__ gold,
-    double* __restrict__ u, int64_t n, int tile, int K, int nblk, double* __restrict__ partials) {
+    const double* g, const double* __restrict__ f, double* gold, double* __restrict__ u,
+    int64_t n, int tile, int K, int nblk, double* __restrict__ partials) {
   const int blk = blockIdx.x, tid = threadIdx.x;
   double sdd = 0.0, snn = 0.0, mx = 0.0, bad = 0.0;
   for (int64_t i = (int64_t)blk * kCorrThreads + tid; i < n; i += (int64_t)nblk * kCorrThreads) {
