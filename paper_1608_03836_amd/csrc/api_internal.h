@@ -109,6 +109,8 @@ inline bool overlaps(const void* a, size_t na, const void* b, size_t nb) {
 // least kPipeMinSlices of them; S = 0 asks for a large launch).
 constexpr int32_t kPipeMinSlices = 2;
 int kernel_path(wadg_ctx c, bool fp32, int mode, int32_t S);
+// Whether the last FP32 stage of a sweep can store FP64 (StageParams::out_fp64).
+bool stores_fp64(wadg_ctx c, int32_t S);
 // Launch one stage of `mode` with the context's kernel choice and the
 // alternating work-item order.
 int launch_stage(wadg_ctx c, int mode, bool fp32, const wadg::StageParams& p0, void* stream);

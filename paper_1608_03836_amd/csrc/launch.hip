@@ -96,6 +96,13 @@ int64_t sets_of(wadg_ctx c, int32_t S) { return (int64_t)((c->K + 15) / 16) * S;
 
 }  // namespace
 
+// Whether an FP32 stage of S slices runs on the pipelined kernel, whose last
+// stage of a sweep can store FP64 itself.
+bool stores_fp64(wadg_ctx c, int32_t S) {
+  return kernel_path(c, true, wadg::kStage, S) == WADG_KERNEL_PIPE &&
+         !takes_quarter(c, true, sets_of(c, S));
+}
+
 int launch_stage(wadg_ctx c, int mode, bool fp32, const wadg::StageParams& p0, void* stream) {
   const int path = kernel_path(c, fp32, mode, p0.S);
   const bool quarter = takes_quarter(c, fp32, sets_of(c, p0.S));

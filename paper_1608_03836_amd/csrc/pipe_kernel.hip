@@ -69,8 +69,9 @@ namespace {
 using namespace dev;
 
 // What a launch computes: an LSRK stage, one whose residual is not stored
-// (the last of a step), or the right-hand side alone.
-enum Kind { kStep, kLastStep, kRight };
+// (the last of a step), such a stage whose output is stored in FP64 (the last
+// of an FP32-bulk sweep), or the right-hand side alone.
+enum Kind { kStep, kLastStep, kLastWide, kRight };
 
 template <typename R, int N, int NQ>
 struct Pipe {
@@ -325,6 +326,7 @@ struct PipeRun {
   R* qout;
   const R* res;
   R* resw;
+  double* qout64;                       // kLastWide: the output, instead of qout
   size_t slice_vals;
   int g, s0, nit;
   rsrc_t vol, face, nbr;
@@ -624,7 +626,14 @@ __device__ __forceinline__ void pipe_inverse_role(const PipeRun<R>& run, const S
         for (int n = 0; n < NP; ++n) {
           const R r = mad(k.A, resv[n], k.dt * dq[n]);
           const R q = mad(k.B, r, qv[n]);
-          if constexpr (NT)
+          if constexpr (KIND == kLastWide) {
+            const rsrc_t qd = make_rsrc(run.qout64 + grp(s), tile * sizeof(double));
+            constexpr unsigned DP = kWave * sizeof(double);
+            if constexpr (NT)
+              st_nt(qd, lane * 8u, (C * NP + n) * DP, (double)q);
+            else
+              st(qd, lane * 8u, (C * NP + n) * DP, (double)q);
+          } else if constexpr (NT)
             st_nt(qo, kb, (C * NP + n) * KP, q);
           else
             st(qo, kb, (C * NP + n) * KP, q);
@@ -745,6 +754,7 @@ __global__ __launch_bounds__(8 * kWave) void pipe_kernel(const StageParams p, in
   PipeRun<R> run;
   run.qin = static_cast<const R*>(p.Qin);
   run.qout = static_cast<R*>(p.Qout);
+  run.qout64 = static_cast<double*>(p.Qout);
   run.res = static_cast<const R*>(p.res);
   run.resw = static_cast<R*>(p.res_out ? p.res_out : p.res);
   run.slice_vals = (size_t)p.nEG * L::tile;
@@ -853,9 +863,10 @@ int launch_kind(const StageParams& p, int cus, void* stream) {
     if ((int64_t)p.nEG * chunks >= (1LL << 31)) return (int)hipErrorInvalidValue;
     const dim3 grid(p.nEG * chunks), block(8 * kWave);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    // (a right-hand side has two state arrays, a stage three)
+    // (a right-hand side has two state arrays, a stage three; one stored in
+    // FP64 counts twice)
     const int64_t bytes = (int64_t)p.S * p.nEG * Pipe<R, N, NQ>::tile_bytes;
-    if (nt_stores((KIND == kRight ? 2 : 3) * bytes))
+    if (nt_stores((KIND == kRight ? 2 : KIND == kLastWide ? 4 : 3) * bytes))
       hipLaunchKernelGGL((pipe_kernel<R, N, NQ, KIND, true>), grid, block, 0, st, p, chunks);
     else
       hipLaunchKernelGGL((pipe_kernel<R, N, NQ, KIND, false>), grid, block, 0, st, p, chunks);
@@ -866,6 +877,8 @@ int launch_kind(const StageParams& p, int cus, void* stream) {
 template <typename R, int N, int NQ>
 int launch_nq(int mode, const StageParams& p, int cus, void* stream) {
   if (mode == kRhs) return launch_kind<R, N, NQ, kRight>(p, cus, stream);
+  if constexpr (sizeof(R) == sizeof(float))
+    if (p.out_fp64) return launch_kind<R, N, NQ, kLastWide>(p, cus, stream);
   return p.res_dead ? launch_kind<R, N, NQ, kLastStep>(p, cus, stream)
                     : launch_kind<R, N, NQ, kStep>(p, cus, stream);
 }

@@ -92,6 +92,8 @@ struct StageParams {
   int32_t res_dead;      // nonzero (stage mode): the residual this stage writes is never
                          // read -- the last stage of a step, the next step starting with
                          // A = 0 -- so the kernel may drop its store
+  int32_t out_fp64;      // nonzero (FP32 stage with res_dead, pipelined kernel): Qout is a
+                         // double array
   AdjMassParams adj;     // kApplyAMass only
 };
 
