@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("N,nq1,K1D,S,random", [
     (4, 5, 33, 30, False), (4, 6, 41, 23, False), (4, 7, 33, 30, False), (3, 6, 33, 30, False),
     (4, 6, 41, 23, True), (3, 6, 110, 2, False), (4, 5, 90, 3, False), (4, 6, 50, 6, False),
-    (4, 6, 128, 20, False)])
+    (4, 6, 128, 20, False), (4, 5, 160, 3, False)])
 def test_streamed_pipe_equals_split(N, nq1, K1D, S, random):
     import torch
     import paper_1608_03836_amd as W
