@@ -119,11 +119,11 @@ int launch_stage(wadg_ctx c, int mode, bool fp32, const wadg::StageParams& p0, v
 int launch_stage_pair(wadg_ctx c, int mode_a, const wadg::StageParams& a0,
                       const wadg::StageParams& b0, void* stream);
 // Whether a sweep of S slices runs as one launch (quarter_sweep_kernel), and
-// that launch: Qout = Qin (may be the same) advanced by nsteps steps with the
-// stage parameters p.
+// that launch (of many steps: a few): Qout = Qin (may be the same) advanced by
+// nsteps steps with the stage parameters p.
 bool one_launch_sweep(wadg_ctx c, bool fp32, int32_t S);
-int launch_sweep(wadg_ctx c, const double* Qin, double* Qout, const wadg::StageParams& p, int32_t nsteps, bool fp32,
-                 void* stream);
+int launch_sweep(wadg_ctx c, const double* Qin, double* Qout, const wadg::StageParams& p,
+                 int32_t nsteps, bool fp32, void* stream);
 // Stage parameters of the context for S slices (geometry, schedule, penalties).
 wadg::StageParams base_params(wadg_ctx c, int32_t S);
 

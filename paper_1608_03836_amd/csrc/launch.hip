@@ -2,6 +2,8 @@
 // automatic choice), the alternating work-item order, and the stage
 // parameters of a context.
 
+#include <algorithm>
+
 #include "api_internal.h"
 
 namespace wadg {
@@ -170,14 +172,28 @@ bool one_launch_sweep(wadg_ctx c, bool fp32, int32_t S) {
   return sets <= 2 || (sets == 3 && (c->N >= 3 || S <= 4 * c->cus)) || S <= 2 * c->cus;
 }
 
-int launch_sweep(wadg_ctx c, const double* Qin, double* Qout, const wadg::StageParams& p, int32_t nsteps, bool fp32,
-                 void* stream) {
+// A launch of quarter_sweep_kernel holds its CUs until its last step, so a
+// sweep of many steps is cut: at most 512 steps of as many slices as there
+// are CUs, or fewer steps of more slices.  Such a launch takes 7 ms (16
+// elements, N = 3; 31 ms at the slowest kernel measured, 12 us per stage),
+// its start 10 us: below 0.2 %.  A step starts from A = 0 and nothing but the
+// state is carried over (in FP32 exactly, through FP64), so the cut changes
+// no bit.
+int launch_sweep(wadg_ctx c, const double* Qin, double* Qout, const wadg::StageParams& p,
+                 int32_t nsteps, bool fp32, void* stream) {
   wadg::SweepCoefs rk;
   for (int i = 0; i < 5; ++i) {
     rk.A[i] = kRkA[i];
     rk.B[i] = kRkB[i];
   }
-  return wadg::launch_sweep_quarter(c->N, c->nq1, Qin, Qout, p, rk, nsteps, fp32, stream);
+  const int32_t rounds = (p.S - 1) / c->cus + 1;
+  const int32_t most = std::max(1, 512 / rounds);
+  for (int32_t done = 0; done < nsteps; done += std::min(most, nsteps - done)) {
+    int e = wadg::launch_sweep_quarter(c->N, c->nq1, done ? Qout : Qin, Qout, p, rk,
+                                       std::min(most, nsteps - done), fp32, stream);
+    if (e) return e;
+  }
+  return 0;
 }
 
 wadg::StageParams base_params(wadg_ctx c, int32_t S) {
