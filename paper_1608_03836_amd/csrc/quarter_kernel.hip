@@ -705,15 +705,25 @@ int launch_pair_nq(int mode_a, const StageParams& a, const StageParams& b, void*
 }
 
 template <typename R, int N, int NQ, int SETS = 1>
-int launch_sweep_nq(const double* Qin, double* Qout, const StageParams& p, const SweepCoefs& rk, int nsteps,
-                    void* stream) {
+int launch_sweep_nq(const double* Qin, double* Qout, const StageParams& p, const SweepCoefs& rk,
+                    int nsteps, void* stream) {
   using L = Quarter<R, N, NQ>;
   if constexpr (SETS <= L::max_sets) {
-    if (p.K > SETS * kQE) return launch_sweep_nq<R, N, NQ, SETS + 1>(Qin, Qout, p, rk, nsteps, stream);
-    hipLaunchKernelGGL((quarter_sweep_kernel<R, N, NQ, SETS>), dim3(p.S),
-                       dim3(SETS * L::waves * kWave), 0, static_cast<hipStream_t>(stream),
-                       Qin, Qout, p, rk, nsteps);
-    return (int)hipGetLastError();
+    if (p.K > SETS * kQE)
+      return launch_sweep_nq<R, N, NQ, SETS + 1>(Qin, Qout, p, rk, nsteps, stream);
+    // (HIP takes fewer than 2^32 lanes per launch: 11 million slices at six waves)
+    constexpr int threads = SETS * L::waves * kWave;
+    constexpr int64_t most = ((1LL << 32) - 1) / threads;
+    constexpr size_t tile = (size_t)3 * L::NP * kWave;
+    for (int64_t s0 = 0; s0 < p.S; s0 += most) {
+      hipLaunchKernelGGL((quarter_sweep_kernel<R, N, NQ, SETS>),
+                         dim3((unsigned)(p.S - s0 < most ? p.S - s0 : most)), dim3(threads), 0,
+                         static_cast<hipStream_t>(stream), Qin + s0 * tile, Qout + s0 * tile, p, rk,
+                         nsteps);
+      const int e = (int)hipGetLastError();
+      if (e) return e;
+    }
+    return 0;
   } else {
     return (int)hipErrorInvalidValue;
   }

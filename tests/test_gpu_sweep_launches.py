@@ -1,6 +1,7 @@
 """GPU: the one-launch sweep of small meshes in more than one launch -- many
-steps, which would hold their CUs throughout -- gives the split kernel's bits,
-and no launch takes more than a bounded share of the steps."""
+steps, which would hold their CUs throughout, or more slices than a launch has
+lanes for -- gives the split kernel's bits, and no launch takes more than a
+bounded share of the steps."""
 
 import numpy as np
 import pytest
@@ -42,3 +43,17 @@ def test_cut_sweep_equals_split(K1D, S, nsteps):
         out.append((sol.download(Q, S), sol.download(Q32, S)))
     for a, b in zip(*out):
         assert np.isfinite(a).all() and np.array_equal(a, b)
+
+
+def test_more_slices_than_a_launch_has_lanes():
+    """Recorded, never run: no launch of an accepted size passes 2^32 lanes."""
+    from paper_1608_03836_amd import binding as B
+    S = 11_500_000
+    print("CASE", f"sweep launches S={S}", flush=True)
+    W, mesh, sol = _solver(1, 4, 5)                  # two sets of three waves
+    Q = 1 << 40                                      # (addresses of nothing)
+    for call in (lambda s: B.wadg_integrate(sol.ctx, Q, 2 * Q, S, 1e-3, 1, s),
+                 lambda s: B.wadg_integrate_fp32(sol.ctx, Q, 2 * Q, S, 1e-3, 1, s)):
+        nodes = kernel_nodes(call)
+        assert sum(g for g, _ in nodes) == S
+        assert all(g * b < 2 ** 32 for g, b in nodes)
