@@ -61,17 +61,17 @@ __device__ __forceinline__ double quad_square(const double (&x)[(N + 1) * (N + 1
 }
 
 // PAIRED: six waves, field f's A - B by wave f and its B by wave 3 + f;
-// else B is absent, and three waves.
+// else B is absent, and three waves.  Workgroup b: item item0 + b.
 template <int N, int NQ, bool PAIRED>
 __global__ __launch_bounds__((PAIRED ? 6 : 3) * kWave) void l2_partial_kernel(
     const double* __restrict__ A, const double* __restrict__ B, const double* __restrict__ vol,
-    int nEG, int K, double* __restrict__ partials) {
+    int item0, int nEG, int K, double* __restrict__ partials) {
   constexpr ct::Tables<N, NQ> tb = ct::make_tables<N, NQ>();
   constexpr int NP = (N + 1) * (N + 1), NQ2 = NQ * NQ, W = PAIRED ? 6 : 3;
   constexpr size_t tile = (size_t)3 * NP * kWave;
   __shared__ double wj[NQ2 * kWave];
   __shared__ double part[6];
-  const int item = blockIdx.x;
+  const int item = item0 + (int)blockIdx.x;
   const int s = item / nEG, g = item - s * nEG;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
   const int f = w % 3;
@@ -135,14 +135,20 @@ __global__ __launch_bounds__(kWave) void l2_final_kernel(const double* __restric
 template <int N, int NQ>
 int launch_nq(const double* A, const double* B, const double* vol, int32_t S, int32_t nEG,
               int32_t K, double* partials, double* out, hipStream_t st) {
-  if (B)
-    hipLaunchKernelGGL((l2_partial_kernel<N, NQ, true>), dim3(S * nEG), dim3(6 * kWave), 0, st, A,
-                       B, vol, nEG, K, partials);
-  else
-    hipLaunchKernelGGL((l2_partial_kernel<N, NQ, false>), dim3(S * nEG), dim3(3 * kWave), 0, st, A,
-                       A, vol, nEG, K, partials);
-  int e = (int)hipGetLastError();
-  if (e) return e;
+  // (HIP takes fewer than 2^32 lanes per launch: 11 million items at six waves)
+  const int threads = (B ? 6 : 3) * kWave;
+  const int64_t most = ((1LL << 32) - 1) / threads, items = (int64_t)S * nEG;
+  for (int64_t i = 0; i < items; i += most) {
+    const dim3 grid((unsigned)(items - i < most ? items - i : most));
+    if (B)
+      hipLaunchKernelGGL((l2_partial_kernel<N, NQ, true>), grid, dim3(threads), 0, st, A, B, vol,
+                         (int)i, nEG, K, partials);
+    else
+      hipLaunchKernelGGL((l2_partial_kernel<N, NQ, false>), grid, dim3(threads), 0, st, A, A, vol,
+                         (int)i, nEG, K, partials);
+    const int e = (int)hipGetLastError();
+    if (e) return e;
+  }
   hipLaunchKernelGGL(l2_final_kernel, dim3(S), dim3(kWave), 0, st, partials, nEG, out);
   return (int)hipGetLastError();
 }
