@@ -28,8 +28,9 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_HBM_GBS = 8000.0
-# wadg_kernel_in_use value -> kernel name (WADG_KERNEL_STREAMED .. _PIPE)
-KERNEL_NAMES = {1: "stage_kernel", 2: "resident_kernel", 3: "split_kernel", 4: "pipe_kernel"}
+# wadg_launch_kernel value -> kernel name (WADG_KERNEL_STREAMED .. _SWEEP)
+KERNEL_NAMES = {1: "stage_kernel", 2: "resident_kernel", 3: "split_kernel", 4: "pipe_kernel",
+                5: "quarter_kernel", 6: "quarter_sweep_kernel"}
 
 
 def parse():
@@ -247,7 +248,7 @@ def run_fp32(args):
                   {"workload": prob.name, "path": "fp32-bulk", "elements": K, "degree": N,
                    "nq1": prob.nq1, "slices": S, "lsrk_steps_per_slice": prob.nsteps,
                    "parallelism": "single-gpu"})
-    k = KERNEL_NAMES[sol.kernel_in_use(fp32=True)]
+    k = KERNEL_NAMES[sol.kernel_in_use(fp32=True, S=S)]
     # the events bracket the whole call: 5 nsteps stage launches plus the two
     # FP64<->FP32 conversions at the ends of the sweep
     kname = f"{k}<float,{N},{prob.nq1}>"
@@ -505,7 +506,7 @@ def main():
     if args.tile_groups:
         sol.set_schedule(args.tile_groups, args.tile_slices)
     sol.set_kernel(kernel_choice(W, args.kernel))
-    kname = KERNEL_NAMES[sol.kernel_in_use()]
+    kname = KERNEL_NAMES[sol.kernel_in_use(S=prob.S)]
     kname += f"<double,{prob.N},{prob.nq1}>"
     S, K, N = prob.S, prob.K, prob.N
     Q = sol.upload(prob.Q0)

@@ -69,6 +69,9 @@ extern "C" {
 #define WADG_KERNEL_RESIDENT 2  /* geometry held in LDS per element group    */
 #define WADG_KERNEL_SPLIT 3     /* one work item over four waves            */
 #define WADG_KERNEL_PIPE 4      /* persistent, pipelined over slice runs    */
+/* chosen automatically only (wadg_launch_kernel) */
+#define WADG_KERNEL_QUARTER 5   /* 16 elements per workgroup, spread over lanes */
+#define WADG_KERNEL_SWEEP 6     /* a slice's whole sweep in one workgroup   */
 
 typedef struct wadg_ctx_s* wadg_ctx;
 typedef struct wadg_batch_s* wadg_batch;
@@ -291,7 +294,7 @@ int wadg_adjoint(wadg_ctx ctx, const double* chk, const double* seed, double* gr
  *   copies in a last virtual slice are neither computed into the state nor
  *   written (their values in Q are unspecified).  0 returns to the item
  *   schedule of wadg_batch_set_schedule.  Default where the kernel's LDS
- *   plan fits (N <= 3 with nq1 <= N + 2): the length, 1 to 64, whose runs
+ *   plan fits (N <= 2, or N = 3 with nq1 <= 5): the length, 1 to 64, whose runs
  *   fill the CUs best; else 0.  Returns
  *   WADG_E_UNSUPPORTED for run_slices > 0 where it does not fit.
  * wadg_batch_set_schedule: item schedule (and run_slices = 0).  wg_per_cu
@@ -418,44 +421,52 @@ int wadg_set_schedule(wadg_ctx ctx, int32_t groups_per_tile, int32_t slices_per_
  *     slices; ignores wadg_set_schedule.  Its FP64 geometry fits for N <= 2,
  *     or N = 3 with nq1 <= 5; elsewhere a RESIDENT request falls back to
  *     the streamed kernel for that precision.
- *   WADG_KERNEL_PIPE: LSRK stages (FP64 and FP32-bulk): one
- *     512-thread workgroup per CU (two in FP32 where both fit in LDS) that
- *     owns one element group and a run of its slices, keeps the group's
- *     geometry on chip for the whole run, streams the next slice's input
- *     tile into LDS while computing the current one, and applies one
- *     slice's mass inverse and update while the next slice's volume and
- *     face terms are formed (a two-stage pipeline over the slices); ignores
- *     wadg_set_schedule.
- *     Needs two input tiles, the metric planes, the face terms, the
- *     handed-over load vectors and the pressure mass weights in LDS (FP64:
- *     N <= 3 with nq1 <= N + 2; FP32: every N, nq1); launches of fewer than
- *     two slices, right-hand sides and the adjoint's launches take the
- *     split kernel.  Launches whose state (Q in, Q out and the residual)
- *     exceeds 512 MB store their outputs and load the residual with the
- *     non-temporal cache hint.
- *   WADG_KERNEL_AUTO (default): LSRK stages (FP64 and FP32) of two or more
- *     slices take the pipelined kernel where it fits, else the split
- *     kernel; right-hand-side launches, where the geometry fits on chip
- *     (wadg_kernel_in_use: WADG_KERNEL_RESIDENT), the pipelined kernel too,
- *     else the split kernel -- the fastest measured on MI355X.  In place of
- *     the split kernel, FP64 stages and right-hand sides with enough slices
- *     per workgroup run on a form of the pipelined kernel that reads the
- *     geometry again for each slice.  Launches of few elements (all slices together: up to 24 per CU in FP64, 32 to 64
- *     in FP32) take a kernel that spreads each element over several lanes,
- *     and the sweep of a mesh of few elements (one workgroup: up to 64,
- *     fewer at high degree or with many slices) runs as one launch.
+ *   WADG_KERNEL_PIPE: LSRK stages (FP64 and FP32-bulk): one 512-thread
+ *     workgroup per CU (more where they fit in LDS and registers) that owns
+ *     one element group and a run of its slices, keeps the group's geometry
+ *     on chip for the whole run, streams the next slice's input tile into
+ *     LDS while computing the current one, and applies one slice's mass
+ *     inverse and update while the next slice's volume and face terms are
+ *     formed (a two-stage pipeline over the slices); ignores
+ *     wadg_set_schedule.  Needs two input tiles, the metric planes, the face
+ *     terms, the handed-over load vectors and the pressure mass weights in
+ *     LDS (FP64: N <= 2, or N = 3 with nq1 <= 5; FP32: every N, nq1);
+ *     launches of fewer than two slices, right-hand sides and the adjoint's
+ *     launches take the split kernel.  Launches whose state (Q in, Q out and
+ *     the residual) exceeds 512 MB store their outputs and load the residual
+ *     with the non-temporal cache hint.
+ *   WADG_KERNEL_AUTO (default), the fastest measured on MI355X: LSRK stages
+ *     of two or more slices and right-hand sides of any number take the
+ *     pipelined kernel where it fits, else (FP64) a form of it that reads the
+ *     geometry again for each slice, where there are enough slices per
+ *     workgroup, else the split kernel.  Launches of few elements (all slices
+ *     together, up to 16 to 64 per CU by degree and precision) take a kernel
+ *     that spreads each element over several lanes, and the sweep of a mesh
+ *     of few elements (one workgroup: up to 64, fewer at high degree or with
+ *     many slices) runs in one launch, or a few of many steps.
  * All variants give bitwise-identical results.  The adjoint's operator
- * launches (apply-A) take the split kernel under AUTO and SPLIT, else the
- * streamed kernel (the resident kernel has no apply-A mode).  Returns
- * WADG_E_INVALID for an
- * unknown value and WADG_E_UNSUPPORTED when the resident or pipelined
- * kernel is requested for an (N, nq1) whose FP64 data do not fit. */
+ * launches (apply-A) take the split kernel under AUTO and SPLIT (AUTO, few
+ * elements: the kernel for those), else the streamed kernel (the resident
+ * kernel has no apply-A mode).  Returns WADG_E_INVALID for an unknown value
+ * and WADG_E_UNSUPPORTED when the resident or pipelined kernel is requested
+ * for an (N, nq1) whose FP64 data do not fit. */
 int wadg_set_kernel(wadg_ctx ctx, int32_t kernel);
 
-/* The kernel variant that `ctx` uses in launches of many slices for LSRK
- * stages (rhs == 0; FP64 for fp32 == 0, FP32-bulk for fp32 != 0) or for
- * wadg_rhs (rhs != 0, fp32 == 0).  kernel: host out. */
+/* The base variant of `ctx`, from its kernel choice, N, nq1 and precision
+ * alone, for LSRK stages (rhs == 0; FP64 for fp32 == 0, FP32-bulk for fp32
+ * != 0) or for wadg_rhs (rhs != 0, fp32 == 0).  Of an explicit choice it is
+ * the kernel that runs (two or more slices).  The automatic choice starts
+ * from it -- the pipelined kernel where it fits, else SPLIT; for wadg_rhs
+ * RESIDENT where the geometry fits on chip, else SPLIT -- and by the number
+ * of elements and slices runs another in its place: wadg_launch_kernel tells
+ * which.  kernel: host out. */
 int wadg_kernel_in_use(wadg_ctx ctx, int32_t rhs, int32_t fp32, int32_t* kernel);
+
+/* The kernel that a call with S slices runs: the stages of wadg_integrate
+ * (rhs == 0, fp32 == 0) or wadg_integrate_fp32 (fp32 != 0), or wadg_rhs (rhs
+ * != 0, fp32 == 0); WADG_KERNEL_SWEEP where the sweep runs in one workgroup
+ * per slice.  kernel: host out. */
+int wadg_launch_kernel(wadg_ctx ctx, int32_t rhs, int32_t fp32, int32_t S, int32_t* kernel);
 
 /* Static description of a status code; never NULL. */
 const char* wadg_status_string(int status);

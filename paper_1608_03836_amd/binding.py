@@ -33,6 +33,8 @@ WADG_KERNEL_STREAMED = 1
 WADG_KERNEL_RESIDENT = 2
 WADG_KERNEL_SPLIT = 3
 WADG_KERNEL_PIPE = 4
+WADG_KERNEL_QUARTER = 5
+WADG_KERNEL_SWEEP = 6
 WADG_CFL_MAX = 1.25
 WADG_NORMS_NOALLOC_MAX_S = 1024
 TILE_LANES = 64
@@ -119,6 +121,8 @@ def _load():
                                         ctypes.c_int32, ctypes.POINTER(ctypes.c_double), vp]),
         "wadg_kernel_in_use": (ctypes.c_int, [vp, ctypes.c_int32, ctypes.c_int32,
                                               ctypes.POINTER(ctypes.c_int32)]),
+        "wadg_launch_kernel": (ctypes.c_int, [vp, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32,
+                                              ctypes.POINTER(ctypes.c_int32)]),
         "wadg_status_string": (ctypes.c_char_p, [ctypes.c_int]),
         "wadg_last_error": (ctypes.c_char_p, []),
     }
@@ -137,7 +141,7 @@ EXPORTED = ("wadg_quadrature_points", "wadg_geometry", "wadg_cfl_number", "wadg_
             "wadg_norms_workspace_bytes", "wadg_norms", "wadg_norms_noalloc",
             "wadg_l2_norms_workspace_bytes",
             "wadg_l2_norms", "wadg_set_schedule", "wadg_set_kernel", "wadg_kernel_in_use",
-            "wadg_set_c2_scale", "wadg_adjoint_workspace_bytes", "wadg_forward_checkpoints",
+            "wadg_launch_kernel", "wadg_set_c2_scale", "wadg_adjoint_workspace_bytes", "wadg_forward_checkpoints",
             "wadg_adjoint", "wadg_batch_create", "wadg_batch_destroy", "wadg_batch_layout",
             "wadg_batch_workspace_bytes", "wadg_batch_integrate", "wadg_batch_set_schedule",
             "wadg_batch_set_runs",
@@ -408,6 +412,13 @@ def wadg_set_kernel(ctx, kernel):
 def wadg_kernel_in_use(ctx, rhs=False, fp32=False):
     out = ctypes.c_int32()
     _check(LIB.wadg_kernel_in_use(ctx, 1 if rhs else 0, 1 if fp32 else 0, ctypes.byref(out)))
+    return out.value
+
+
+def wadg_launch_kernel(ctx, S, rhs=False, fp32=False):
+    out = ctypes.c_int32()
+    _check(LIB.wadg_launch_kernel(ctx, 1 if rhs else 0, 1 if fp32 else 0, int(S),
+                                  ctypes.byref(out)))
     return out.value
 
 

@@ -313,6 +313,17 @@ int wadg_kernel_in_use(wadg_ctx ctx, int32_t rhs, int32_t fp32, int32_t* kernel)
   return WADG_OK;
 }
 
+int wadg_launch_kernel(wadg_ctx ctx, int32_t rhs, int32_t fp32, int32_t S, int32_t* kernel) {
+  int st = check_slices(ctx, S);
+  if (st) return st;
+  if (!kernel) return fail(WADG_E_INVALID, "kernel is NULL");
+  if (rhs && fp32) return fail(WADG_E_INVALID, "there is no FP32 right-hand-side launch");
+  *kernel = !rhs && one_launch_sweep(ctx, fp32 != 0, S)
+                ? WADG_KERNEL_SWEEP
+                : launch_kernel(ctx, rhs ? wadg::kRhs : wadg::kStage, fp32 != 0, S);
+  return WADG_OK;
+}
+
 int wadg_rhs(wadg_ctx ctx, const double* Q, double* dQdt, int32_t S, void* stream) {
   int st = check_slices(ctx, S);
   if (st) return st;
@@ -385,7 +396,8 @@ int sweep_fp32_from(wadg_ctx ctx, const double* src, double* Q, void* work, int3
   int e = wadg::launch_to_fp32(src, q0, n, stream);
   if (e) return hip_fail((hipError_t)e, "conversion kernel launch");
   p.res = res;
-  const bool wide = stores_fp64(ctx, S);
+  // (the pipelined kernel can, StageParams::out_fp64)
+  const bool wide = launch_kernel(ctx, wadg::kStage, true, S) == WADG_KERNEL_PIPE;
   float* cur = q0;
   for (int stp = 0; stp < nsteps; ++stp)
     for (int i = 0; i < 5; ++i) {

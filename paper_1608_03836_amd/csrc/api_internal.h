@@ -104,13 +104,12 @@ inline bool overlaps(const void* a, size_t na, const void* b, size_t nb) {
   return pa < pb + nb && pb < pa + na;
 }
 
-// The stage kernel that runs for this context, precision and launch mode.
-// The kernel variant for a launch of S slices (WADG_KERNEL_PIPE needs at
-// least kPipeMinSlices of them; S = 0 asks for a large launch).
+// The selectable kernel variant that a launch of S slices starts from
+// (WADG_KERNEL_PIPE needs at least kPipeMinSlices of them).
 constexpr int32_t kPipeMinSlices = 2;
 int kernel_path(wadg_ctx c, bool fp32, int mode, int32_t S);
-// Whether the last FP32 stage of a sweep can store FP64 (StageParams::out_fp64).
-bool stores_fp64(wadg_ctx c, int32_t S);
+// The kernel that a launch of S slices runs: launch_stage's choice.
+int launch_kernel(wadg_ctx c, int mode, bool fp32, int32_t S);
 // Launch one stage of `mode` with the context's kernel choice and the
 // alternating work-item order.
 int launch_stage(wadg_ctx c, int mode, bool fp32, const wadg::StageParams& p0, void* stream);

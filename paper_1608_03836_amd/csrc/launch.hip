@@ -22,19 +22,16 @@ const double kRkB[5] = {1432997174477.0 / 9575080441755.0,
                         3134564353537.0 / 4481467310338.0,
                         2277821191437.0 / 14882151754819.0};
 
-// Kernel variant that runs for this context, precision and launch mode.
-// Automatic choice, from measurement on MI355X (64x64 and 128x128
-// elements, N = 3, FP64 and FP32): LSRK stages of two or more slices take
-// the pipelined kernel where its LDS plan fits, else the split-work
-// kernel; right-hand-side launches take the resident-geometry kernel where
-// the geometry fits in LDS (launch_stage runs them on the pipelined kernel,
-// which keeps it on chip as well), else the split-work kernel (for long
-// enough slice runs launch_stage uses the pipelined kernel's form that
-// streams the geometry, takes_streamed_pipe); the adjoint's
-// apply-A launches take the split-work kernel (the resident kernel has no
-// apply-A mode, so an explicit RESIDENT or STREAMED choice runs them
-// streamed).  Automatic launches of few elements take the quarter kernel
-// instead of any of these (takes_quarter).
+// The base variant of a launch: the selectable kernel that its context,
+// precision and mode lead to without regard to its size (but S = 1).  An
+// explicit choice launches it; the automatic one starts from it
+// (launch_kernel).  From measurement on MI355X (64x64 and 128x128 elements, N
+// = 3, FP64 and FP32): LSRK stages of two or more slices take the pipelined
+// kernel where its LDS plan fits, else the split-work kernel; right-hand
+// sides the resident-geometry kernel where the geometry fits in LDS, else
+// the split-work kernel; the adjoint's apply-A launches the split-work
+// kernel (the resident kernel has no apply-A mode, so an explicit RESIDENT
+// or STREAMED choice runs them streamed).
 int kernel_path(wadg_ctx c, bool fp32, int mode, int32_t S) {
   if (mode == wadg::kStage && (c->kernel == WADG_KERNEL_PIPE || c->kernel == WADG_KERNEL_AUTO) &&
       S >= kPipeMinSlices && wadg::pipe_supported(c->N, c->nq1, fp32))
@@ -86,13 +83,12 @@ bool takes_quarter(wadg_ctx c, bool fp32, int64_t sets) {
 // 17.9; nq1 = 5, 50x50 and 32: 59 -> 46.8, 50 -> 37.8; nq1 = 7: 94 -> 77, 82
 // -> 64; N = 3, nq1 = 6, 64x64 and 64: 164 -> 112, 135 -> 86; 24x24 and 30
 // (2, 3) 24.3 -> 18.5; 200x200 and 3 (8, 3 x 4) 84 -> 76.
-bool takes_streamed_pipe(wadg_ctx c, const wadg::StageParams& p) {
-  if (c->kernel != WADG_KERNEL_AUTO || wadg::pipe_supported(c->N, c->nq1, false)) return false;
-  const int64_t chunks = wadg::pipe_chunks(p.nEG, p.S, c->cus);
+bool takes_streamed_pipe(wadg_ctx c, int32_t S) {
+  const int64_t nEG = c->groups(), chunks = wadg::pipe_chunks((int)nEG, S, c->cus);
   // (workgroups one after another on a CU)
-  const int64_t runs = ((int64_t)p.nEG * chunks + c->cus - 1) / c->cus;
-  const int64_t steps = runs * ((p.S + chunks - 1) / chunks + 1);
-  const int64_t rounds = ((int64_t)p.nEG * p.S + c->cus - 1) / c->cus;
+  const int64_t runs = (nEG * chunks + c->cus - 1) / c->cus;
+  const int64_t steps = runs * ((S + chunks - 1) / chunks + 1);
+  const int64_t rounds = (nEG * S + c->cus - 1) / c->cus;
   return 3 * rounds >= 2 * steps;
 }
 
@@ -100,41 +96,44 @@ int64_t sets_of(wadg_ctx c, int32_t S) { return (int64_t)((c->K + 15) / 16) * S;
 
 }  // namespace
 
-// Whether an FP32 stage of S slices runs on the pipelined kernel, whose last
-// stage of a sweep can store FP64 itself.
-bool stores_fp64(wadg_ctx c, int32_t S) {
-  return kernel_path(c, true, wadg::kStage, S) == WADG_KERNEL_PIPE &&
-         !takes_quarter(c, true, sets_of(c, S));
+// The kernel of a launch of S slices: the base variant, or in an automatic
+// choice the quarter kernel (few elements) or the pipelined kernel (right-hand
+// sides, and FP64 launches whose geometry it streams).
+//
+// An automatic right-hand side whose geometry fits on chip runs on the
+// pipelined kernel, which holds it there too and overlaps one slice's loads
+// and face terms with another's mass inverse.  Measured on MI355X against
+// the resident kernel, bitwise the same: 128x128 elements, N = 3, nq1 = 5,
+// 256 slices 1,178 -> 909 us, 2 slices 20.4 -> 16.6, 1 slice 18.5 -> 11.1;
+// 81x81, N = 2, 24 slices 39.9 -> 30.7; 64x64, N = 1, 64 slices 28.4 ->
+// 19.3 (never slower at any size measured).
+int launch_kernel(wadg_ctx c, int mode, bool fp32, int32_t S) {
+  const int base = kernel_path(c, fp32, mode, S);
+  if (c->kernel != WADG_KERNEL_AUTO) return base;
+  if (takes_quarter(c, fp32, sets_of(c, S))) return WADG_KERNEL_QUARTER;
+  if (!fp32 && wadg::pipe_supported(c->N, c->nq1, false))
+    return mode == wadg::kRhs ? WADG_KERNEL_PIPE : base;
+  if (!fp32 && (mode == wadg::kStage || mode == wadg::kRhs) && takes_streamed_pipe(c, S))
+    return WADG_KERNEL_PIPE;
+  return base;
 }
 
 int launch_stage(wadg_ctx c, int mode, bool fp32, const wadg::StageParams& p0, void* stream) {
-  const int path = kernel_path(c, fp32, mode, p0.S);
-  const bool quarter = takes_quarter(c, fp32, sets_of(c, p0.S));
-  // An automatic right-hand side whose geometry fits on chip runs on the
-  // pipelined kernel, which holds it there too and overlaps one slice's loads
-  // and face terms with another's mass inverse.  Measured on MI355X against
-  // the resident kernel, bitwise the same: 128x128 elements, N = 3, nq1 = 5,
-  // 256 slices 1,178 -> 909 us, 2 slices 20.4 -> 16.6, 1 slice 18.5 -> 11.1;
-  // 81x81, N = 2, 24 slices 39.9 -> 30.7; 64x64, N = 1, 64 slices 28.4 ->
-  // 19.3 (never slower at any size measured).
-  const bool pipe_rhs = mode == wadg::kRhs && c->kernel == WADG_KERNEL_AUTO &&
-                        wadg::pipe_supported(c->N, c->nq1, false);
-  const bool streamed_pipe =
-      !fp32 && (mode == wadg::kStage || mode == wadg::kRhs) && takes_streamed_pipe(c, p0);
-  if ((path == WADG_KERNEL_PIPE || pipe_rhs || streamed_pipe) && !quarter)
+  const int kernel = launch_kernel(c, mode, fp32, p0.S);
+  if (kernel == WADG_KERNEL_PIPE)
     return fp32 ? wadg::launch_stage_pipe_fp32(c->N, c->nq1, p0, c->cus, stream)
                 : wadg::launch_stage_pipe(c->N, c->nq1, mode, p0, c->cus, stream);
   // alternate the item order from one launch to the next (item_of)
   wadg::StageParams p = p0;
   c->order_flip ^= 1;
   p.reverse = (int32_t)c->order_flip;
-  if (quarter)
+  if (kernel == WADG_KERNEL_QUARTER)
     return fp32 ? wadg::launch_stage_quarter_fp32(c->N, c->nq1, p, stream)
                 : wadg::launch_stage_quarter(c->N, c->nq1, mode, p, stream);
-  if (path == WADG_KERNEL_SPLIT)
+  if (kernel == WADG_KERNEL_SPLIT)
     return fp32 ? wadg::launch_stage_split_fp32(c->N, c->nq1, p, stream)
                 : wadg::launch_stage_split(c->N, c->nq1, mode, p, stream);
-  if (path == WADG_KERNEL_RESIDENT) {
+  if (kernel == WADG_KERNEL_RESIDENT) {
     const int ranges = wadg::resident_ranges(p.nEG, p.S, c->cus);
     return fp32 ? wadg::launch_stage_resident_fp32(c->N, c->nq1, p, ranges, stream)
                 : wadg::launch_stage_resident(c->N, c->nq1, mode, p, ranges, stream);

@@ -132,7 +132,11 @@ class Solver:
         """WADG_KERNEL_AUTO, _STREAMED, _RESIDENT, _SPLIT or _PIPE (see wadg_set_kernel)."""
         B.wadg_set_kernel(self.ctx, kernel)
 
-    def kernel_in_use(self, rhs=False, fp32=False):
+    def kernel_in_use(self, rhs=False, fp32=False, S=None):
+        """The kernel that calls with S slices run; without S the variant that
+        the choice starts from (see wadg_kernel_in_use)."""
+        if S is not None:
+            return B.wadg_launch_kernel(self.ctx, S, rhs, fp32)
         return B.wadg_kernel_in_use(self.ctx, rhs, fp32)
 
     # -- sensitivities ---------------------------------------------------

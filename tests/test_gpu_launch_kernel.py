@@ -1,0 +1,63 @@
+"""GPU: wadg_launch_kernel names the kernel that a call runs, read off the
+workgroups that the call launches: 512 threads (pipelined), a workgroup per 16
+elements (quarter) or per slice (whole sweep), else four waves per item (split)
+or the resident kernel's ranges."""
+
+import pytest
+
+from graph_nodes import kernel_nodes
+from workloads import periodic_quad_mesh
+
+pytestmark = pytest.mark.gpu
+
+
+def launched(W, sol, S, rhs=False, fp32=False):
+    """The kernel of the second stage (of the only launch) of a call."""
+    Q = sol.empty_state(S)
+    if rhs:
+        out = sol.empty_state(S)
+        nodes = kernel_nodes(lambda s: sol.rhs(Q, S, out=out, stream=s))
+    else:
+        work = sol.workspace_fp32(S) if fp32 else sol.workspace(S)
+        run = sol.integrate_fp32 if fp32 else sol.integrate
+        nodes = kernel_nodes(lambda s: run(Q, S, 1e-3, 1, work=work, stream=s))
+    if not rhs and len(nodes) == 1 and nodes[0][0] == S:
+        return W.WADG_KERNEL_SWEEP
+    G, sets = -(-sol.K // 64), -(-sol.K // 16)
+    stages = nodes[:] if rhs else [n for n in nodes if nodes.count(n) >= 4]
+    assert stages, nodes
+    grid, threads = stages[0]
+    if threads == 512:
+        return W.WADG_KERNEL_PIPE
+    if grid == sets * S and threads == 64 * (1 + (2 * sol.nq1 + 3) // 4):
+        return W.WADG_KERNEL_QUARTER
+    assert (grid, threads) == (G * S, 256), nodes
+    return W.WADG_KERNEL_SPLIT
+
+
+@pytest.mark.parametrize("N,nq1,K1D,S,rhs,fp32", [
+    (3, 5, 4, 100, False, False), (3, 5, 4, 100, False, True), (3, 5, 4, 100, True, False),
+    (3, 5, 9, 4, False, False), (3, 5, 64, 40, False, False), (3, 5, 64, 40, False, True),
+    (3, 5, 64, 1, False, False), (3, 5, 64, 40, True, False), (3, 5, 100, 1, True, False),
+    (4, 6, 50, 32, False, False), (4, 6, 50, 32, True, False), (4, 6, 50, 6, False, False),
+    (3, 6, 64, 64, False, False), (3, 6, 9, 2, True, False), (2, 4, 81, 24, False, True)])
+def test_launch_kernel_names_what_runs(N, nq1, K1D, S, rhs, fp32):
+    import paper_1608_03836_amd as W
+    print("CASE", f"launch kernel N={N} nq1={nq1} K1D={K1D} S={S} rhs={rhs} fp32={fp32}",
+          flush=True)
+    sol = W.Solver(periodic_quad_mesh(K1D, N, eps=0.05), nq1=nq1)
+    assert sol.kernel_in_use(rhs=rhs, fp32=fp32, S=S) == launched(W, sol, S, rhs, fp32)
+    for kernel in (W.WADG_KERNEL_STREAMED, W.WADG_KERNEL_SPLIT):
+        sol.set_kernel(kernel)
+        assert sol.kernel_in_use(rhs=rhs, fp32=fp32, S=S) == kernel
+
+
+def test_launch_kernel_refuses():
+    import paper_1608_03836_amd as W
+    sol = W.Solver(periodic_quad_mesh(4, 3, eps=0.05))
+    for S, rhs, fp32 in ((0, False, False), (1, True, True)):
+        with pytest.raises(W.WadgError) as e:
+            W.wadg_launch_kernel(sol.ctx, S, rhs, fp32)
+        assert e.value.status == W.binding.WADG_E_INVALID
+    with pytest.raises(W.WadgError):
+        sol.set_kernel(W.WADG_KERNEL_QUARTER)
