@@ -51,22 +51,36 @@ int kernel_path(wadg_ctx c, bool fp32, int mode, int32_t S) {
 
 namespace {
 
-// Whether an automatic launch over `sets` sets of 16 elements (all slices)
-// takes the quarter kernel: up to about as many sets as fill the CUs once.
-// Its launch takes the time of one short item, but each workgroup reads its
-// own copy of the geometry and exchanges every intermediate through LDS, so
-// it loses where several sets queue on a CU.  Measured on MI355X (256 CUs),
-// one stage launch against the kernel of kernel_path, FP64: N = 3, nq1 = 5:
-// 8.3 -> 5.8 us at 64 sets, 9.4 -> 6.9 at 256, 9.6 -> 8.6 at 384, 10.5 ->
-// 10.2 at 576, 11.7 -> 12.1 at 1024; N = 3, nq1 = 6: 12.2 -> 11.7 at 384,
-// 12.0 -> 12.8 at 484; N = 1: 5.0 -> 4.7 at 384, 4.8 -> 5.0 at 484; N = 4,
+int64_t sets_of(wadg_ctx c, int32_t S) { return (int64_t)((c->K + 15) / 16) * S; }
+
+// Whether an automatic launch over `sets` sets of 16 elements, S slices, takes
+// the quarter kernel: up to about as many sets as fill the CUs once.  Its
+// launch takes the time of one short item, but each workgroup reads its own
+// copy of the geometry and exchanges every intermediate through LDS, so it
+// loses where several sets queue on a CU.  Measured on MI355X (256 CUs), one
+// launch against the kernel that otherwise runs, us:
+//   FP64 stages and the adjoint's launches, N = 3, nq1 = 5: 8.3 -> 5.8 at 64
+// sets, 9.4 -> 6.9 at 256, 9.6 -> 8.6 at 384, 11.7 -> 12.1 at 1024; N = 4,
 // nq1 = 6: 12.7 -> 9.0 at 64, 15.8 -> 13.9 at 384, 14.8 -> 16.0 at 576.
-// FP32 items are half the bytes and registers: N = 3: 6.7 -> 4.8 at 64, 9.3
-// -> 8.5 at 1024; N = 2: 5.4 -> 4.9 at 484, 6.33 -> 6.39 at 1024.
-bool takes_quarter(wadg_ctx c, bool fp32, int64_t sets) {
+// Stages stop at 256 sets at nq1 <= 3, whose items are short (N = 2, nq1 = 3:
+// 5.8 -> 6.0 at 384), and at N = 3, nq1 = 6, whose instance spills (12.0 ->
+// 12.7 at 324, 12.2 -> 13.1 at 381; right-hand sides 9 % faster there).
+//   FP32 of one slice, against the split kernel: N = 3: 6.7 -> 4.8 at 64 sets,
+// 9.3 -> 8.5 at 1024; N = 2: 5.4 -> 4.9 at 484, 6.33 -> 6.39 at 1024.
+//   FP32 of more slices, against the pipelined kernel, which holds two
+// workgroups per CU: N = 3, nq1 = 5: 10 % faster at 512 sets, 1 % at 576, 7.9
+// -> 8.5 at 800, 8.2 -> 9.5 at 1024; N = 4, nq1 = 5: 9.3 -> 9.6 at 628, 10.2
+// -> 12.4 at 1024; nq1 = 7: 13.0 -> 15.4 at 785; N = 1, 2: nq1 <= 3 even at 256
+// to 384, 3.8 -> 4.05 at 512; nq1 = 4, 5: 4 % faster at 512.
+bool takes_quarter(wadg_ctx c, int mode, bool fp32, int32_t S, int64_t sets) {
   if (c->kernel != WADG_KERNEL_AUTO) return false;
   const int64_t cus = c->cus;
-  return sets <= (!fp32 ? cus * 3 / 2 : c->N >= 3 ? cus * 4 : cus * 2);
+  const bool shortest = c->nq1 <= 3;
+  if (!fp32)
+    return sets <= (mode == wadg::kStage && (shortest || (c->N == 3 && c->nq1 == 6))
+                        ? cus : cus * 3 / 2);
+  if (S == 1) return sets <= (c->N >= 3 ? cus * 4 : cus * 2);
+  return sets <= (c->N >= 3 ? cus * 9 / 4 : shortest ? cus : cus * 2);
 }
 
 // Whether an automatic FP64 stage or right-hand side whose geometry does not
@@ -92,8 +106,6 @@ bool takes_streamed_pipe(wadg_ctx c, int32_t S) {
   return 3 * rounds >= 2 * steps;
 }
 
-int64_t sets_of(wadg_ctx c, int32_t S) { return (int64_t)((c->K + 15) / 16) * S; }
-
 }  // namespace
 
 // The kernel of a launch of S slices: the base variant, or in an automatic
@@ -110,7 +122,7 @@ int64_t sets_of(wadg_ctx c, int32_t S) { return (int64_t)((c->K + 15) / 16) * S;
 int launch_kernel(wadg_ctx c, int mode, bool fp32, int32_t S) {
   const int base = kernel_path(c, fp32, mode, S);
   if (c->kernel != WADG_KERNEL_AUTO) return base;
-  if (takes_quarter(c, fp32, sets_of(c, S))) return WADG_KERNEL_QUARTER;
+  if (takes_quarter(c, mode, fp32, S, sets_of(c, S))) return WADG_KERNEL_QUARTER;
   if (!fp32 && wadg::pipe_supported(c->N, c->nq1, false))
     return mode == wadg::kRhs ? WADG_KERNEL_PIPE : base;
   if (!fp32 && (mode == wadg::kStage || mode == wadg::kRhs) && takes_streamed_pipe(c, S))
@@ -147,7 +159,7 @@ int launch_stage_pair(wadg_ctx c, int mode_a, const wadg::StageParams& a0,
   wadg::StageParams a = a0, b = b0;
   c->order_flip ^= 1;
   a.reverse = b.reverse = (int32_t)c->order_flip;
-  if (takes_quarter(c, false, sets_of(c, a0.S) + sets_of(c, b0.S)))
+  if (takes_quarter(c, mode_a, false, a0.S, sets_of(c, a0.S) + sets_of(c, b0.S)))
     return wadg::launch_stage_quarter_pair(c->N, c->nq1, mode_a, a, b, stream);
   return wadg::launch_stage_pair(c->N, c->nq1, mode_a, a, b, stream);
 }
