@@ -165,22 +165,42 @@ int launch_stage_pair(wadg_ctx c, int mode_a, const wadg::StageParams& a0,
 }
 
 // One launch for the whole sweep where a slice's mesh fits in one workgroup
-// (quarter_sweep_kernel): always for one or two sets of 16 elements; for
-// three, where N >= 3 or there are few slices; for four (whose workgroups
-// are held to 128 registers per lane, one per CU), where there are few.
-// Otherwise many slices fill the chip better from the stage kernels.
-// Measured per stage on MI355X (256 CUs), the stage launches against this
-// one, FP64, N = 3, nq1 = 5: 16 elements, 1 slice 7.9 -> 2.6 us, 4096 slices
-// 61.6 -> 19.0; 25 elements, 1 slice 8.0 -> 3.4, 4096 slices 67 -> 52; 36
-// elements, 2048 slices 35.2 -> 35.4; 64 elements, 512 slices 15.5 -> 13.7,
-// 2048 slices 36.7 -> 53.8.  N = 1, nq1 = 3, 36 elements, 4096 slices: 19.9
-// -> 27.4; N = 2, nq1 = 5: 46.5 -> 53.2.
+// (quarter_sweep_kernel), by its sets of 16 elements:
+//   one or two: always;
+//   three, N >= 3: always, but for N = 3, nq1 = 5 with more than 8 slices per
+// CU whose stages find their three arrays in the 256 MB memory-side cache;
+//   three, N <= 2: up to 4 slices per CU; four: up to 2.  Beyond, many slices
+// fill the chip better from the stage kernels;
+//   FP64 workgroups of 15 or 16 waves at N >= 3, nq1 >= 5 (three sets at nq1 =
+// 7, else four), which are held to 128 registers per lane and spill: only
+// where there are too many slices for the quarter kernel's stages, and few
+// enough to run at once.
+// Measured per stage on MI355X (256 CUs), us, the stage launches against this
+// one: N = 3, nq1 = 5, FP64: 16 elements, 1 slice 7.9 -> 2.6, 4096 slices 61.6
+// -> 19.0; 25 elements, 4096 slices 64 -> 49; 36 elements, 2048 slices 34.4 ->
+// 33.1, 3072 47.1 -> 49.0, 16384 294 -> 261; 64 elements, 1 slice 6.0 -> 7.6 (one step; 5.4 ->
+// 5.7 of eight), 128 slices 1.41x, 512 1.18x, 2048 36.7 -> 53.8.  FP32: 36
+// elements, 2048 slices 21.3 -> 19.7, 4096 34.0 -> 38.5, 6144 49.4 -> 57.6,
+// 12288 1.25x; nq1 = 4 and 6 there 1.17x, 1.06x.  nq1 = 6, FP64: 64 elements, 1
+// slice 8.4 -> 10.3, 256 slices 1.48x, 512 19.5 -> 22.7.  N = 4: 36 elements,
+// FP64, nq1 = 5, 6: 1.13x to 2.5x at any number; nq1 = 7: 1 slice 8.8 ->
+// 14.4, 256 1.31x, 1024 54 -> 61, 16384 739 -> 967 (25 elements: 1.28x to 3.0x); FP32
+// 1.2x to 2.7x.  N = 1, nq1 = 3, 36 elements: 1024 slices 1.22x, 4096 19.9 ->
+// 27.4; N = 2, nq1 = 5: 1.24x, 46.5 -> 53.2.
 bool one_launch_sweep(wadg_ctx c, bool fp32, int32_t S) {
   if (c->kernel != WADG_KERNEL_AUTO ||
       c->K > wadg::quarter_sweep_elements(c->N, c->nq1, fp32))
     return false;
   const int sets = (c->K + 15) / 16;
-  return sets <= 2 || (sets == 3 && (c->N >= 3 || S <= 4 * c->cus)) || S <= 2 * c->cus;
+  const int64_t cus = c->cus;
+  if (sets <= 2) return true;
+  if (!fp32 && c->N >= 3 && c->nq1 >= 5 && sets == (c->nq1 == 7 ? 3 : 4))
+    return S <= (c->nq1 == 5 ? 2 * cus : cus) &&
+           !takes_quarter(c, wadg::kStage, fp32, S, sets_of(c, S));
+  if (sets == 4) return S <= 2 * cus;
+  if (c->N < 3) return S <= 4 * cus;
+  const int64_t arrays = 3 * (int64_t)c->state_doubles(S) * (fp32 ? 4 : 8);
+  return !(c->N == 3 && c->nq1 == 5 && S > 8 * cus && arrays <= (int64_t)256 << 20);
 }
 
 // A launch of quarter_sweep_kernel holds its CUs until its last step, so a

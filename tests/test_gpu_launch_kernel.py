@@ -83,3 +83,35 @@ def test_quarter_kernel_where_it_is_faster(N, nq1, K1D, S, rhs, fp32, kernel):
     sol = W.Solver(periodic_quad_mesh(K1D, N, eps=0.05), nq1=nq1)
     assert launched(W, sol, S, rhs, fp32) == getattr(W, "WADG_KERNEL_" + kernel)
     assert sol.kernel_in_use(rhs=rhs, fp32=fp32, S=S) == getattr(W, "WADG_KERNEL_" + kernel)
+
+
+# Where a sweep in one workgroup per slice stops to pay
+SWEEP_EDGES = [  # N, nq1, K1D, S, fp32, in one launch
+    (3, 5, 6, 2048, True, True), (3, 5, 6, 2049, True, False), (3, 5, 6, 7281, True, False),
+    (3, 5, 6, 7282, True, True), (3, 5, 6, 2048, False, True), (3, 5, 6, 3640, False, False),
+    (3, 5, 6, 3641, False, True), (3, 6, 6, 4096, True, True), (3, 4, 6, 4096, True, True),
+    (4, 6, 6, 4096, False, True), (4, 7, 6, 1, False, False), (4, 7, 6, 256, False, True),
+    (4, 7, 6, 257, False, False), (4, 7, 6, 1024, True, True), (4, 7, 5, 1024, False, True),
+    (3, 6, 8, 256, False, True), (3, 6, 8, 257, False, False), (3, 6, 8, 512, True, True),
+    (3, 5, 8, 96, False, False), (3, 5, 8, 97, False, True), (3, 6, 8, 64, False, False),
+    (3, 5, 8, 512, False, True), (3, 5, 8, 513, False, False), (2, 4, 6, 1024, False, True),
+    (2, 4, 6, 1025, True, False)]
+
+
+@pytest.mark.parametrize("N,nq1,K1D,S,fp32,one", SWEEP_EDGES)
+def test_one_launch_sweep_where_it_is_faster(N, nq1, K1D, S, fp32, one):
+    """The rule's edges, and the split kernel's bits on both sides of them."""
+    import torch
+    import paper_1608_03836_amd as W
+    print("CASE", f"sweep edge N={N} nq1={nq1} K1D={K1D} S={S} fp32={fp32}", flush=True)
+    sol = W.Solver(periodic_quad_mesh(K1D, N, eps=0.05, warp="skew", rotate_seed=K1D), nq1=nq1)
+    assert (launched(W, sol, S, fp32=fp32) == W.WADG_KERNEL_SWEEP) == one
+    g = torch.Generator(device="cuda").manual_seed(K1D)
+    Q0 = torch.randn(S * sol.slice_doubles, dtype=torch.float64, device="cuda", generator=g)
+    out = []
+    for kernel in (W.WADG_KERNEL_SPLIT, W.WADG_KERNEL_AUTO):
+        sol.set_kernel(kernel)
+        Q = Q0.clone()
+        (sol.integrate_fp32 if fp32 else sol.integrate)(Q, S, 0.1 / (K1D * (N + 1) ** 2), 2)
+        out.append(Q.view(S, -1, 3 * (N + 1) ** 2, 64)[..., :sol.K])
+    assert torch.isfinite(out[0]).all() and torch.equal(*out)
