@@ -187,13 +187,17 @@ RunLists best_placement(const wadg_batch b, int run_slices, double* end) {
 // Default slices per run: the length whose last run ends first, the longest
 // of equals.  Long runs pay the prologue and the pipeline's drain less often,
 // short ones fill the CUs of a small batch and even out the last wave.
-// Measured on MI355X per stage, N = 3, nq1 = 5, uneven problems of 4 to 256
-// elements and 8 to 128 slices, runs of 16 on whole problems against this
-// choice of length and placement: 3 problems 58 -> 9.9 us, 12 56.6 -> 19.3, 30
-// 99.7 -> 47.6, 60 125 -> 114, 120 164 -> 155, 250 417 -> 404.  Over 20
-// batches, N = 1..3, the choice was within 13 % of the best length tried, and
-// never slower than runs of 16 by more than 3 %.
+// Measured on MI355X per stage, uneven problems of 4 to 256 elements and 8 to
+// 128 slices, runs of 16 on whole problems against this choice of length and
+// placement, N = 3, nq1 = 5: 3 problems 58 -> 9.9 us, 12 56.6 -> 19.3, 30 99.7
+// -> 47.6, 60 125 -> 114, 120 164 -> 155, 250 417 -> 404; over 28 batches never
+// slower by more than 1 %.  At N <= 2 the steps are short and a CU may hold
+// several workgroups, which the model leaves out: over 92 batches a length
+// that it put less than 7 % ahead was up to 28 % slower than runs of 16 (N =
+// 1, nq1 = 2, 152 problems: 38.4 us, 49.0 with 48), so those are kept there,
+// after which two were slower, by 3 and 6 %.
 int default_run_slices(const wadg_batch b) {
+  constexpr int kLong = 16;
   int best = 1, last = 0;
   double best_end = -1.0;
   const int most = *std::max_element(b->Sv.begin(), b->Sv.end());
@@ -210,6 +214,7 @@ int default_run_slices(const wadg_batch b) {
       best = L;
     }
   }
+  if (b->N <= 2 && best_end > 0.93 * runs_end(place_runs(b, kLong, true), b->cus)) return kLong;
   return best;
 }
 
