@@ -304,9 +304,10 @@ int wadg_adjoint(wadg_ctx ctx, const double* chk, const double* seed, double* gr
  *   1 round-robin over problems.
  * Results are bitwise independent of the schedule and of the runs.
  * wadg_batch_tune: the autotuner -- times one stage of every candidate
- *   (runs of 4, 8, 16, 32, 128 slices where the pipelined kernel fits; 1, 2,
- *   4, 8 persistent workgroups per CU or one per item, both orders) reps
- *   times on the device, keeps the fastest and returns it (host out:
+ *   (the schedule on entry; runs of the default length and of 4, 8, 16, 32,
+ *   128 slices where the pipelined kernel fits; 1, 2, 4, 8 persistent
+ *   workgroups per CU or one per item, both orders) reps times on the
+ *   device, keeps the fastest and returns it (host out:
  *   wg_per_cu, order, run_slices -- 0 unless the pipelined kernel won --
  *   and best_us per stage).  Q is read only; work is scratch.  Synchronises
  *   `stream`.

@@ -602,20 +602,21 @@ int wadg_batch_tune(wadg_batch b, const double* Q, double* work, const double* d
     if (e0) (void)hipEventDestroy(e0);
     return hip_fail(hipErrorUnknown, "hipEventCreate");
   }
-  // candidates: the pipelined kernel with runs of 4..128 slices per
-  // workgroup (tile = one element group x a run of slices); persistent grids
-  // of 1, 2, 4, 8 two-wave workgroups per CU (streamed kernel) or one
-  // four-wave workgroup per item (split kernel), in both item orders; each
-  // timed on a stage with a residual read (Q is only read, the workspace is
-  // scratch)
+  // candidates: the schedule on entry, first, so that another is taken only
+  // if it is faster; the pipelined kernel with runs of the default length and
+  // of 4..128 slices per workgroup (tile = one element group x a run of
+  // slices); persistent grids of 1, 2, 4, 8 two-wave workgroups per CU
+  // (streamed kernel) or one four-wave workgroup per item (split kernel), in
+  // both item orders; each timed on a stage with a residual read (Q is only
+  // read, the workspace is scratch)
   struct Cand { int m, o, r; };
-  std::vector<Cand> cands;
+  const Cand c0{b->grid_mult, b->order, b->run_slices};
+  std::vector<Cand> cands{c0};
   if (wadg::batch_pipe_supported(b->N, b->nq1))
-    for (int r : {4, 8, 16, 32, 128}) cands.push_back({0, 0, r});
+    for (int r : {default_run_slices(b), 4, 8, 16, 32, 128}) cands.push_back({0, 0, r});
   for (int o = 0; o < 2; ++o)
     for (int m : {1, 2, 4, 8, 0}) cands.push_back({m, o, 0});
   double best = 1e300;
-  const Cand c0{b->grid_mult, b->order, b->run_slices};
   Cand bc = c0;
   auto apply = [&](const Cand& c) {
     int s = wadg_batch_set_schedule(b, c.m, c.o);

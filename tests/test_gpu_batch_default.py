@@ -38,3 +38,20 @@ def test_default_runs_leave_16_for_a_clear_gain(N, nq1, count, shapes, kept):
     default = _workgroups(batch)
     batch.set_runs(16)
     assert (default == _workgroups(batch)) == kept
+
+
+def test_tune_times_the_schedule_it_finds():
+    """1,280 slices of one group: runs of 5 keep every CU busy for 7 steps, the
+    nearest lengths for 10 and more, and the created batch has them."""
+    import torch
+    import paper_1608_03836_amd as W
+    print("CASE batch tune", flush=True)
+    batch = W.Batch([periodic_quad_mesh(8, 3, eps=0.05)], [1280])
+    created = _workgroups(batch)
+    Q = torch.zeros(batch.total, dtype=torch.float64, device="cuda")
+    for runs in (None, 5, 16):                        # as created; the caller's; a slower one
+        if runs:
+            batch.set_runs(runs)
+        _, _, tuned, us = batch.tune(Q, np.full(1, 1e-3), reps=10)
+        assert tuned == 5 and us > 0.0
+        assert _workgroups(batch) == created
