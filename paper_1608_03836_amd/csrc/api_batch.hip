@@ -103,53 +103,67 @@ constexpr int kXcds = 8;
 using Run = std::array<int32_t, 4>;                // problem, group, first slice, slices
 using RunLists = std::vector<std::vector<Run>>;    // per XCD, in the order it takes them
 
-// Runs of the pipelined kernel: for every problem and element group of its
-// virtual mesh, the virtual slices in which the group holds a real element
-// (all but, possibly, the last), cut into ceil(n / run_slices) runs of
-// nearly equal length; each XCD takes its runs longest first (runs of equal
-// length problem-major).  The neighbour traces a group reads should come
-// from tiles its own XCD has just loaded, so with `whole` a problem goes to
-// one XCD as a whole (largest first, to the XCD with the least work so far);
-// otherwise the problems' runs (slice range by slice range, all groups of
-// each) are dealt out in eight contiguous shares of equal work.
-RunLists place_runs(const wadg_batch b, int run_slices, bool whole) {
-  std::vector<std::vector<Run>> per(b->nprob);
+// Virtual slices of problem i in which its group g holds a real element: all
+// but, possibly, the last.
+int group_slices(const wadg_batch b, int i, int g) {
+  return b->Sv[i] - (g * wadg::kWave >= last_slice_elements(b, i) ? 1 : 0);
+}
+
+// The XCD of each problem, if problems go to one XCD as a whole: largest
+// first, to the XCD with the least work so far.
+std::vector<int> whole_xcds(const wadg_batch b) {
   std::vector<int64_t> work(b->nprob, 0);
-  int64_t total = 0;
+  std::vector<int> order(b->nprob), xcd(b->nprob);
   for (int i = 0; i < b->nprob; ++i) {
+    order[i] = i;
+    for (int g = 0; g < b->nEG[i]; ++g) work[i] += group_slices(b, i, g);
+  }
+  std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return work[x] > work[y]; });
+  int64_t load[kXcds] = {};
+  for (int i : order) {
+    int x = 0;
+    for (int y = 1; y < kXcds; ++y)
+      if (load[y] < load[x]) x = y;
+    load[x] += work[i];
+    xcd[i] = x;
+  }
+  return xcd;
+}
+
+// Runs of the pipelined kernel: for every problem and element group of its
+// virtual mesh, the virtual slices in which the group holds a real element,
+// cut into ceil(n / run_slices) runs of nearly equal length; each XCD takes
+// its runs longest first (runs of equal length problem-major).  The neighbour
+// traces a group reads should come from tiles its own XCD has just loaded, so
+// a problem goes to one XCD as a whole (`whole`: the problems' XCDs) or
+// (NULL) the problems' runs, slice range by slice range, all groups of each,
+// are dealt out in eight contiguous shares of equal work.
+RunLists place_runs(const wadg_batch b, int run_slices, const std::vector<int>* whole) {
+  RunLists xcd(kXcds);
+  int64_t total = 0, done = 0;
+  if (!whole)
+    for (int i = 0; i < b->nprob; ++i)
+      for (int g = 0; g < b->nEG[i]; ++g) total += group_slices(b, i, g);
+  std::vector<Run> runs;
+  for (int i = 0; i < b->nprob; ++i) {
+    runs.clear();
     for (int g = 0; g < b->nEG[i]; ++g) {
-      const int n = b->Sv[i] - (g * wadg::kWave >= last_slice_elements(b, i) ? 1 : 0);
-      const int c = (n + run_slices - 1) / run_slices;
+      const int n = group_slices(b, i, g), c = (n + run_slices - 1) / run_slices;
       for (int j = 0; j < c; ++j) {
         const int s0 = (int)((int64_t)j * n / c), s1 = (int)((int64_t)(j + 1) * n / c);
-        per[i].push_back({i, g, s0, s1 - s0});
+        runs.push_back({i, g, s0, s1 - s0});
       }
-      work[i] += n;
     }
-    total += work[i];
-  }
-  RunLists xcd(kXcds);
-  if (whole) {
-    std::vector<int> order(b->nprob);
-    for (int i = 0; i < b->nprob; ++i) order[i] = i;
-    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return work[x] > work[y]; });
-    int64_t load[kXcds] = {};
-    for (int i : order) {
-      int x = 0;
-      for (int y = 1; y < kXcds; ++y)
-        if (load[y] < load[x]) x = y;
-      load[x] += work[i];
-      xcd[x].insert(xcd[x].end(), per[i].begin(), per[i].end());
+    if (whole) {
+      auto& l = xcd[(*whole)[i]];
+      l.insert(l.end(), runs.begin(), runs.end());
+      continue;
     }
-  } else {
-    int64_t done = 0;
-    for (auto& runs : per) {
-      std::stable_sort(runs.begin(), runs.end(),
-                       [](const Run& u, const Run& v) { return u[2] < v[2]; });
-      for (const Run& r : runs) {
-        xcd[std::min<int64_t>(kXcds - 1, done * kXcds / std::max<int64_t>(1, total))].push_back(r);
-        done += r[3];
-      }
+    std::stable_sort(runs.begin(), runs.end(),
+                     [](const Run& u, const Run& v) { return u[2] < v[2]; });
+    for (const Run& r : runs) {
+      xcd[std::min<int64_t>(kXcds - 1, done * kXcds / std::max<int64_t>(1, total))].push_back(r);
+      done += r[3];
     }
   }
   for (auto& l : xcd)
@@ -157,31 +171,62 @@ RunLists place_runs(const wadg_batch b, int run_slices, bool whole) {
   return xcd;
 }
 
-// When the last run ends, in items: each XCD's CUs take its runs in order,
-// one at a time, a run of n slices lasting n + 1 pipeline steps and a
-// prologue (geometry and first tile) of about one more.
-double runs_end(const RunLists& xcd, int cus) {
-  constexpr double kOverhead = 2.0;
+// How many runs of each length an XCD takes, and when the last of them ends,
+// in items: its CUs take them longest first, one at a time, a run of n slices
+// lasting n + 1 pipeline steps and a prologue (geometry and first tile) of
+// about one more.
+using RunCounts = std::vector<int64_t>;             // [length]
+constexpr double kRunOverhead = 2.0;
+
+double runs_end(const RunCounts& count, int cus) {
   double end = 0.0;
-  for (const auto& l : xcd) {
-    std::vector<double> h(std::max(1, cus / kXcds), 0.0);     // a heap, earliest free CU first
-    for (const Run& r : l) {
+  std::vector<double> h(std::max(1, cus / kXcds), 0.0);       // a heap, earliest free CU first
+  for (size_t n = count.size(); n-- > 1;)
+    for (int64_t r = 0; r < count[n]; ++r) {
       std::pop_heap(h.begin(), h.end(), std::greater<double>());
-      h.back() += r[3] + kOverhead;
+      h.back() += n + kRunOverhead;
       end = std::max(end, h.back());
       std::push_heap(h.begin(), h.end(), std::greater<double>());
     }
-  }
   return end;
 }
 
-// The placement of runs of at most run_slices that ends first; dealing the
-// problems out has to gain a tenth, for the traces that then cross XCDs.
-RunLists best_placement(const wadg_batch b, int run_slices, double* end) {
-  RunLists whole = place_runs(b, run_slices, true), dealt = place_runs(b, run_slices, false);
-  const double ew = runs_end(whole, b->cus), ed = runs_end(dealt, b->cus);
-  *end = std::min(ew, ed / 0.9);
-  return ed < 0.9 * ew ? dealt : whole;
+// When the last run of at most run_slices ends with the problems whole on
+// their XCDs and dealt out, the latter only where it may be the choice (else
+// infinite): dealing has to gain a tenth, for the traces that then cross XCDs.
+// Both infinite where neither can end before `limit`.
+constexpr double kDealtGain = 0.9;
+
+void placement_ends(const wadg_batch b, int run_slices, const std::vector<int>& whole,
+                    double limit, double* whole_end, double* dealt_end) {
+  const int most = *std::max_element(b->Sv.begin(), b->Sv.end());
+  std::vector<RunCounts> count(kXcds, RunCounts(most + 1, 0));
+  int64_t items = 0, runs = 0;
+  int longest = 0;
+  for (int i = 0; i < b->nprob; ++i)
+    for (int g = 0; g < b->nEG[i]; ++g) {
+      const int n = group_slices(b, i, g), c = (n + run_slices - 1) / run_slices;
+      if (n == 0) continue;
+      count[whole[i]][n / c] += c - n % c;
+      if (n % c) count[whole[i]][n / c + 1] += n % c;
+      items += n;
+      runs += c;
+      longest = std::max(longest, (n + c - 1) / c);
+    }
+  // no placement ends before its longest run, or all runs shared out evenly
+  const int cus = kXcds * std::max(1, b->cus / kXcds);
+  const double least = std::max(longest + kRunOverhead, (items + kRunOverhead * runs) / cus);
+  *whole_end = *dealt_end = INFINITY;
+  if (least >= limit) return;
+  *whole_end = 0.0;
+  for (const auto& c : count) *whole_end = std::max(*whole_end, runs_end(c, b->cus));
+  if (least >= kDealtGain * *whole_end) return;
+  *dealt_end = 0.0;
+  for (const auto& l : place_runs(b, run_slices, nullptr)) {
+    RunCounts c(most + 1, 0);
+    for (const Run& r : l) ++c[r[3]];
+    *dealt_end = std::max(*dealt_end, runs_end(c, b->cus));
+  }
 }
 
 // Default slices per run: the length whose last run ends first, the longest
@@ -198,8 +243,10 @@ RunLists best_placement(const wadg_batch b, int run_slices, double* end) {
 // after which two were slower, by 3 and 6 %.
 int default_run_slices(const wadg_batch b) {
   constexpr int kLong = 16;
+  const std::vector<int> whole = whole_xcds(b);
+  double ew, ed;
   int best = 1, last = 0;
-  double best_end = -1.0;
+  double best_end = INFINITY;
   const int most = *std::max_element(b->Sv.begin(), b->Sv.end());
   for (int L : {64, 48, 40, 32, 28, 24, 20, 16, 14, 12, 10, 8, 7, 6, 5, 4, 3, 2, 1}) {
     L = std::min(L, most);
@@ -207,14 +254,17 @@ int default_run_slices(const wadg_batch b) {
     last = L;
     // (short runs of many items only cost time, here and there)
     if (L < 16 && b->items / L > 16 * (int64_t)b->cus) break;
-    double end;
-    best_placement(b, L, &end);
-    if (best_end < 0.0 || end < best_end) {
+    placement_ends(b, L, whole, best_end, &ew, &ed);
+    const double end = std::min(ew, ed / kDealtGain);
+    if (end < best_end) {
       best_end = end;
       best = L;
     }
   }
-  if (b->N <= 2 && best_end > 0.93 * runs_end(place_runs(b, kLong, true), b->cus)) return kLong;
+  if (b->N <= 2 && best != kLong) {
+    placement_ends(b, kLong, whole, INFINITY, &ew, &ed);
+    if (best_end > 0.93 * ew) return kLong;
+  }
   return best;
 }
 
@@ -222,8 +272,10 @@ int default_run_slices(const wadg_batch b) {
 // b on XCD b % 8), so it is laid out per block; blocks past the end of their
 // XCD's list get an empty run (problem -1).  Uploaded like the work list.
 int batch_upload_runs(wadg_batch b) {
-  double end;
-  const RunLists xcd = best_placement(b, b->run_slices, &end);
+  const std::vector<int> whole = whole_xcds(b);
+  double ew, ed;
+  placement_ends(b, b->run_slices, whole, INFINITY, &ew, &ed);
+  const RunLists xcd = place_runs(b, b->run_slices, ed < kDealtGain * ew ? nullptr : &whole);
   size_t longest = 0;
   for (auto& l : xcd) longest = std::max(longest, l.size());
   std::vector<int32_t> r;
