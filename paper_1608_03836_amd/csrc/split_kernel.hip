@@ -406,15 +406,8 @@ __device__ __forceinline__ void split_run(const StageParams& p, int bid, int nb,
   constexpr unsigned KP = kWave * sizeof(R);
 
   const int w = item_of(bid, nb, p.reverse);
-  const int Be = p.tile_groups, Bs = p.tile_slices, nEG = p.nEG;
-  const int sb = w / (Bs * nEG);
-  const int r = w - sb * Bs * nEG;
-  const int bs = min(Bs, p.S - sb * Bs);
-  const int eb = r / (Be * bs);
-  const int r2 = r - eb * Be * bs;
-  const int be = min(Be, nEG - eb * Be);
-  const int s = sb * Bs + r2 / be;
-  const int eg = eb * Be + r2 % be;
+  int s, eg;
+  item_coords(w, p.nEG, p.S, p.tile_groups, p.tile_slices, s, eg);
   const int lane = threadIdx.x & (kWave - 1);
 
   const R* Qin = static_cast<const R*>(p.Qin);
@@ -442,7 +435,7 @@ __device__ __forceinline__ void split_run(const StageParams& p, int bid, int nb,
                      (am.a != 0.0 && am.r_prev) ? tb : 0u);
   }
   split_item<R, N, NQ, MODE>(B, stage_scalars<R>(p), eg * kWave + lane < p.K, tq, xf, xm, p.adj,
-                             s * nEG + eg);
+                             s * p.nEG + eg);
 }
 
 template <typename R, int N, int NQ, int MODE>

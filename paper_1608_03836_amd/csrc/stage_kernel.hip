@@ -210,17 +210,8 @@ __global__ __launch_bounds__(2 * kWave) void stage_kernel(const StageParams p) {
   __shared__ __attribute__((aligned(16))) R tq[tile];
 
   const int w = item_of(blockIdx.x, gridDim.x, p.reverse);
-  // work item -> (slice, element group): tiles of Be element groups x Bs
-  // slices, ordered (slice block, element block), slice-major inside a tile
-  const int Be = p.tile_groups, Bs = p.tile_slices, nEG = p.nEG;
-  const int sb = w / (Bs * nEG);
-  const int r = w - sb * Bs * nEG;
-  const int bs = min(Bs, p.S - sb * Bs);
-  const int eb = r / (Be * bs);
-  const int r2 = r - eb * Be * bs;
-  const int be = min(Be, nEG - eb * Be);
-  const int s = sb * Bs + r2 / be;
-  const int eg = eb * Be + r2 % be;
+  int s, eg;
+  item_coords(w, p.nEG, p.S, p.tile_groups, p.tile_slices, s, eg);
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & (kWave - 1);
