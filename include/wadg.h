@@ -423,12 +423,12 @@ int wadg_set_schedule(wadg_ctx ctx, int32_t groups_per_tile, int32_t slices_per_
  *     or N = 3 with nq1 <= 5; elsewhere a RESIDENT request falls back to
  *     the streamed kernel for that precision.
  *   WADG_KERNEL_PIPE: LSRK stages (FP64 and FP32-bulk): one 512-thread
- *     workgroup per CU (more where they fit in LDS and registers) that owns
- *     one element group and a run of its slices, keeps the group's geometry
- *     on chip for the whole run, streams the next slice's input tile into
- *     LDS while computing the current one, and applies one slice's mass
- *     inverse and update while the next slice's volume and face terms are
- *     formed (a two-stage pipeline over the slices); ignores
+ *     workgroup per CU (two where both fit in LDS) that owns one element
+ *     group and a run of its slices, keeps the group's geometry on chip for
+ *     the whole run, streams the next slice's input tile into LDS while
+ *     computing the current one, and applies one slice's mass inverse and
+ *     update while the next slice's volume and face terms are formed (a
+ *     two-stage pipeline over the slices); ignores
  *     wadg_set_schedule.  Needs two input tiles, the metric planes, the face
  *     terms, the handed-over load vectors and the pressure mass weights in
  *     LDS (FP64: N <= 2, or N = 3 with nq1 <= 5; FP32: every N, nq1);

@@ -618,15 +618,15 @@ int finish_norms(int32_t S, double* out) {
   return WADG_OK;
 }
 
-// The reduction of wadg_norms into device scratch `partials` (S x 64 x 4)
+// The reduction of wadg_norms into device scratch `partials` (S x up to 64 x 4)
 // and `dout` (S x 4), then the sums copied to `out` (synchronises).
 int run_norms(wadg_ctx ctx, const double* A, const double* B, int32_t S, double* partials,
               double* dout, double* out, void* stream) {
   hipStream_t hs = static_cast<hipStream_t>(stream);
   const int64_t per = (int64_t)ctx->slice_doubles();
   // as many blocks as have a whole round of four values per lane, up to the
-  // scratch's 64: 2,000 slices of 16 elements, N =
-  // 3 (3 blocks): 315 -> 65 us a call
+  // scratch's 64: 2,000 slices of 16 elements, N = 3 (3 blocks), 315 -> 65 us
+  // a call
   const int blocks = (int)std::min<int64_t>(kNormBlocks, (per + 1023) / 1024);
   int e = wadg::launch_norms(A, B, S, per, (int32_t)ctx->tile(), ctx->K, partials, blocks, dout,
                              stream);

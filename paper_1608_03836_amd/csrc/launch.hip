@@ -89,12 +89,12 @@ bool takes_quarter(wadg_ctx c, int mode, bool fp32, int32_t S, int64_t sets) {
 // walks ceil(S / chunks) slices and takes one step more to drain the
 // pipeline, and a CU runs the split kernel's items two at a time; a step
 // takes about two thirds of such a round's time, so the shorter sum decides
-// (a run of one slice per workgroup stays split).  Measured on MI355X (256 CUs), stage and
-// right-hand side, us, split -> pipelined: N = 4, nq1 = 6: 50x50 elements
-// and 32 slices (5 rounds, 7 steps) 72.5 -> 66.4, 64.9 -> 52.8; 128x128 and
-// 64 slices (64, 65) 875 -> 659, 752 -> 514; 50x50 and 12 (2, 3) 30.2 ->
-// 28.1; but 96x96 and 16 (9, 17) 126 -> 142; 50x50 and 6 (1, 2) 16.4 ->
-// 17.9; nq1 = 5, 50x50 and 32: 59 -> 46.8, 50 -> 37.8; nq1 = 7: 94 -> 77, 82
+// (a run of one slice per workgroup stays split).  Measured on MI355X (256
+// CUs), stage and right-hand side, us, split -> pipelined: N = 4, nq1 = 6:
+// 50x50 elements and 32 slices (5 rounds, 7 steps) 72.5 -> 66.4, 64.9 -> 52.8;
+// 128x128 and 64 slices (64, 65) 875 -> 659, 752 -> 514; 50x50 and 12 (2, 3)
+// 30.2 -> 28.1; but 96x96 and 16 (9, 17) 126 -> 142; 50x50 and 6 (1, 2) 16.4
+// -> 17.9; nq1 = 5, 50x50 and 32: 59 -> 46.8, 50 -> 37.8; nq1 = 7: 94 -> 77, 82
 // -> 64; N = 3, nq1 = 6, 64x64 and 64: 164 -> 112, 135 -> 86; 24x24 and 30
 // (2, 3) 24.3 -> 18.5; 200x200 and 3 (8, 3 x 4) 84 -> 76.
 bool takes_streamed_pipe(wadg_ctx c, int32_t S) {

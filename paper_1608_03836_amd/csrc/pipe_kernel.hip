@@ -54,10 +54,11 @@
 // (metric terms) or three (mass weights) ahead of their use, the velocity
 // waves' two metric planes held in registers up to nq1 = 6, and the nodal
 // values read from LDS for each column to make room for them.  What bounds
-// it is the chain of a step's loads and products with two waves per SIMD: at N = 4, nq1 = 6 a step takes 9.5 us (streamed
-// geometry 100 KB per CU and step, 2.7 TB/s over the chip) against 14.5 us
-// for a round of split items.  Held weights or a loop over the columns
-// (63 KB of code instead of 81) were slower or did not fit the registers.
+// it is the chain of a step's loads and products with two waves per SIMD: at
+// N = 4, nq1 = 6 a step takes 9.5 us (streamed geometry 100 KB per CU and step,
+// 2.7 TB/s over the chip) against 14.5 us for a round of split items.  Held
+// weights or a loop over the columns (63 KB of code instead of 81) were slower
+// or did not fit the registers.
 
 #include <hip/hip_runtime.h>
 
@@ -447,7 +448,8 @@ __device__ __forceinline__ void pipe_volume_role(const PipeRun<R>& run, int lane
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int q = 0; q < NQ2; ++q) gm[h][q] = ldr<R>(run.vol, kb, ((C - 1 + 2 * h) * NQ2 + q) * KP);
+      for (int q = 0; q < NQ2; ++q)
+        gm[h][q] = ldr<R>(run.vol, kb, ((C - 1 + 2 * h) * NQ2 + q) * KP);
   }
   auto metric = [&](int i, R (&g)[4][NQ]) {
 #pragma unroll
@@ -942,14 +944,15 @@ int launch_batch_nq(const BatchParams& p, const int32_t* runs, int32_t nruns, vo
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (nt_stores(3 * (int64_t)p.nitems * Pipe<double, N, NQ>::tile_bytes)) {
       if (p.res_dead)
-        hipLaunchKernelGGL((batch_pipe_kernel<N, NQ, kLastStep, true>), grid, block, 0, st, p, runs, nruns);
+        hipLaunchKernelGGL((batch_pipe_kernel<N, NQ, kLastStep, true>), grid, block, 0, st, p, runs,
+                           nruns);
       else
         hipLaunchKernelGGL((batch_pipe_kernel<N, NQ, kStep, true>), grid, block, 0, st, p, runs,
                            nruns);
     } else {
       if (p.res_dead)
-        hipLaunchKernelGGL((batch_pipe_kernel<N, NQ, kLastStep, false>), grid, block, 0, st, p, runs,
-                           nruns);
+        hipLaunchKernelGGL((batch_pipe_kernel<N, NQ, kLastStep, false>), grid, block, 0, st, p,
+                           runs, nruns);
       else
         hipLaunchKernelGGL((batch_pipe_kernel<N, NQ, kStep, false>), grid, block, 0, st, p, runs,
                            nruns);

@@ -27,17 +27,27 @@
 // D deal their pieces to the waves from the last one on, because the face
 // wave holds the most operands.
 //
-// Registers decide how many workgroups a CU holds (four of one wave per SIMD
-// at N <= 3: 128 per lane).  Measured on MI355X, one FP64 stage at N = 3,
-// nq1 = 5 from a stream (an empty launch takes 2.4 us): 16 groups 8.3 -> 5.8
-// us against the split kernel's one item per workgroup, 64 groups 9.4 -> 6.9.
+// A set has 1 + ceil(nq1 / 2) waves (Quarter::waves): 128 threads at nq1 = 2,
+// 192 at 3 and 4, 256 at 5 and 6, 320 at 7.  Registers decide how many
+// workgroups a CU holds: four of one wave per SIMD at N <= 3 (128 per lane),
+// three at N = 4 (168).  FP64 instances that need more spill, and are used all
+// the same where the measured time is shorter: stages at N = 3, nq1 = 4 (9
+// registers) and 6 (63) and N = 4, nq1 = 6 (44), the apply-A + mass mode from
+// N = 3 on (18 at nq1 = 5, 152 in the pair at nq1 = 6), sweeps of four sets from
+// N = 2, nq1 = 5 on (40; 93 at N = 3, nq1 = 5; 177 at nq1 = 6), of three at N
+// = 3, nq1 = 6 and N = 4 (24 to 99; 298 at nq1 = 7) and of two at N = 4, nq1 = 7
+// (160).  No FP32 instance does.
+//
+// Measured on MI355X, one FP64 stage at N = 3, nq1 = 5 from a stream (an empty
+// launch takes 2.4 us): 16 groups 8.3 -> 5.8 us against the split kernel's one
+// item per workgroup, 64 groups 9.4 -> 6.9.
 //
 // quarter_sweep_kernel advances a whole slice of a mesh of few elements
-// through all stages of all steps in one launch: the mesh is one workgroup
+// through all stages of many steps in one launch: the mesh is one workgroup
 // (a set of these waves per 16 elements), the geometry stays in registers,
 // the state in LDS and registers, and neighbour traces are read from LDS.
 // Per stage on 16 elements: 7.9 -> 2.6 us with one slice, 61.6 -> 19.0 with
-// 4096 (it reads and writes the state once per sweep, and no lanes idle).
+// 4096 (it reads and writes the state once per launch, and no lanes idle).
 
 #include <hip/hip_runtime.h>
 
@@ -55,9 +65,9 @@ constexpr int kQE = 16;      // elements per set
 template <typename R, int N, int NQ>
 struct Quarter {
   static constexpr int NP1 = N + 1, NP = NP1 * NP1, NQ2 = NQ * NQ;
-  // Waves of a set: four at NQ = 5 and 6, one per SIMD (a fifth would share
-  // SIMD 0 with the first in every workgroup, which then decides how many
-  // workgroups a CU holds).
+  // Waves of a set: four at NQ = 5 and 6, one per SIMD (a fifth, as at NQ = 7,
+  // shares SIMD 0 with the first in every workgroup, which then decides how
+  // many workgroups a CU holds).
   static constexpr int waves = 1 + (2 * NQ + 3) / 4;
   static constexpr int pieces = 4 * waves;                     // per element and phase
   static_assert(pieces >= 3 * NP1, "one piece per node row");
@@ -82,8 +92,12 @@ struct Quarter {
   // inverse column q = c NQ + i, row b; sums k (cr, cs, cx, cy) of column i,
   // row b; face f, field c, face node (or row) m
   static __device__ constexpr int at_t(int q, int b) { return (b * st + q) * kQE; }
-  static __device__ constexpr int at_c(int k, int i, int b) { return ((k * NP1 + b) * sc + i) * kQE; }
-  static __device__ constexpr int at_f(int f, int c, int m) { return ((c * NP1 + m) * sf + f) * kQE; }
+  static __device__ constexpr int at_c(int k, int i, int b) {
+    return ((k * NP1 + b) * sc + i) * kQE;
+  }
+  static __device__ constexpr int at_f(int f, int c, int m) {
+    return ((c * NP1 + m) * sf + f) * kQE;
+  }
   static constexpr unsigned set = tq + xt + xc + xf;
   // sets of a workgroup that holds a whole mesh
   static constexpr int lds_sets = (int)(160u * 1024u / (set * sizeof(R)));
@@ -133,7 +147,9 @@ struct Lane {
     b = row - c * NP1;
   }
   // byte offset of node a of the lane's row in a tiled state
-  __device__ __forceinline__ unsigned rowoff() const { return kb + (unsigned)(c * NP + NP1 * b) * KP; }
+  __device__ __forceinline__ unsigned rowoff() const {
+    return kb + (unsigned)(c * NP + NP1 * b) * KP;
+  }
 
   // Phase B, first part: the load vector of the lane's row, volume term then
   // face terms in face order 0..3 (faces 0 and 2 are the rows b = 0 and N,
@@ -551,8 +567,8 @@ __device__ __forceinline__ void quarter_run(const StageParams& p, int bid, int n
 }  // namespace
 
 template <typename R, int N, int NQ, int MODE>
-__global__ __launch_bounds__((Quarter<R, N, NQ>::waves * kWave), N <= 3 ? 4 : 3) void quarter_kernel(
-    const StageParams p) {
+__global__ __launch_bounds__((Quarter<R, N, NQ>::waves * kWave),
+                             N <= 3 ? 4 : 3) void quarter_kernel(const StageParams p) {
   __shared__ __attribute__((aligned(1024))) R lds[Quarter<R, N, NQ>::set];
   quarter_run<R, N, NQ, MODE>(p, blockIdx.x, gridDim.x, lds);
 }
@@ -561,8 +577,9 @@ __global__ __launch_bounds__((Quarter<R, N, NQ>::waves * kWave), N <= 3 ? 4 : 3)
 // sets of launch a in mode MA (an apply-A mode), then the LSRK stage sets of
 // launch b.
 template <typename R, int N, int NQ, int MA>
-__global__ __launch_bounds__((Quarter<R, N, NQ>::waves * kWave), N <= 3 ? 4 : 3) void quarter_pair_kernel(
-    const StageParams a, const StageParams b, int na) {
+__global__ __launch_bounds__((Quarter<R, N, NQ>::waves * kWave),
+                             N <= 3 ? 4 : 3) void quarter_pair_kernel(const StageParams a,
+                                                                     const StageParams b, int na) {
   __shared__ __attribute__((aligned(1024))) R lds[Quarter<R, N, NQ>::set];
   if ((int)blockIdx.x < na)
     quarter_run<R, N, NQ, MA>(a, blockIdx.x, na, lds);
@@ -696,7 +713,8 @@ int launch_pair_nq(int mode_a, const StageParams& a, const StageParams& b, void*
   const dim3 grid(na + nb), block(Quarter<double, N, NQ>::waves * kWave);
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (mode_a == kApplyAMass)
-    hipLaunchKernelGGL((quarter_pair_kernel<double, N, NQ, kApplyAMass>), grid, block, 0, st, a, b, na);
+    hipLaunchKernelGGL((quarter_pair_kernel<double, N, NQ, kApplyAMass>), grid, block, 0, st, a, b,
+                       na);
   else if (mode_a == kApplyA)
     hipLaunchKernelGGL((quarter_pair_kernel<double, N, NQ, kApplyA>), grid, block, 0, st, a, b, na);
   else

@@ -215,7 +215,8 @@ __device__ __forceinline__ void pressure_volume_column(int i, const FU& U, const
   R cr[N + 1], cs[N + 1];
   pressure_column_sums<R, N, NQ>(T.V[i], U, V, g, cr, cs);
 #pragma unroll
-  for (int bb = 0; bb <= N; ++bb) pressure_column_add<R, N, NQ>(i, cr[bb], cs[bb], bp + (N + 1) * bb);
+  for (int bb = 0; bb <= N; ++bb)
+    pressure_column_add<R, N, NQ>(i, cr[bb], cs[bb], bp + (N + 1) * bb);
 }
 
 // Velocity volume term, quadrature column i:  (bu, bv) -= sum_j w J l grad p,
